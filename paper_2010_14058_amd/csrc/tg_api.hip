@@ -550,8 +550,15 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     int cus = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     // light groups differ in size up to 512 wedges: many small workgroups
-    // balance them (each clears its LDS map per group anyway)
-    unsigned light_grid = (unsigned)((cus > 0 ? cus : 256) * 1024);
+    // balance them (each clears its LDS map per group anyway).  There is at
+    // most one group per node: a grid of 262,144 workgroups that find no
+    // group costs 0.23 ms per pass (a graph of 20 nodes), 6 us sized by n
+    int64_t light_wgs = (int64_t)(cus > 0 ? cus : 256) * 1024;
+    if (light_wgs > n) light_wgs = n;
+    const unsigned light_grid = (unsigned)light_wgs;
+    // a heavy group has more wedges than the light bucket: none can exist
+    // when the largest possible group fits it (30 us per empty launch)
+    const bool any_heavy = wedge_cap > (uint64_t)g_tune[TG_TUNE_LIGHT_WEDGES];
     for (int pass = 0; pass < 2; ++pass) {
         ca.list = pass == 0 ? la_l : lb_l;
         ca.count_idx = pass == 0 ? C_A_LIGHT : C_B_LIGHT;
@@ -602,7 +609,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
                          ? heavy_hub_ids(L, n, g_tune[TG_TUNE_HUB_LDS]) : 0;
         ca.chunk = heavy_chunk_for(L, pass == 0 ? HEAVY_THREADS_A : HEAVY_THREADS_B, ca.hub_ids,
                                    words32);
-        HIPCHK(launch_cycles(pass, true, ca, (unsigned)y.heavy_slots, st));
+        if (any_heavy) HIPCHK(launch_cycles(pass, true, ca, (unsigned)y.heavy_slots, st));
         timing_mark(pass == 0 ? "cycA_heavy" : "cycB_heavy");
     }
 
@@ -666,7 +673,9 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     else eh.hist_in_lds = ea.hist_in_lds ? 1 : 0;
     eh.derive_batch = 1;
     if (xyk) eh.hist_in_lds = 0;
-    HIPCHK(launch_edges(true, eh, (unsigned)y.heavy_edge_slots, st));
+    // a heavy edge's smaller end exceeds the cut: none can exist when the
+    // largest degree does not (50 us for an empty launch)
+    if (max_deg > ecut) HIPCHK(launch_edges(true, eh, (unsigned)y.heavy_edge_slots, st));
     timing_mark("edges_heavy");
     if (pa) {
         const PaLayout pl = pa_layout(L);

@@ -1044,10 +1044,11 @@ __attribute__((amdgpu_waves_per_eu(MODE == 0 || MODE == 3 ? 5 : 1))) k_edges_hea
     S.Gw = Gw;
     int tid = threadIdx.x;
     if (input_failed(a.status)) return;
+    uint64_t count = a.counters[C_EDGE_HEAVY];
+    if (blockIdx.x >= count) return;  // more workgroups than edges: nothing to stage
     for (int q = tid; q < TMw; q += NT) TMs[q] = a.TM[q];
     uint32_t bad = 0;
     for (int q = tid; q < hist_words(a); q += NT) hist[q] = 0;
-    uint64_t count = a.counters[C_EDGE_HEAVY];
     __syncthreads();
     while (true) {
         if (tid == 0) s_idx = atomicAdd((unsigned long long *)&a.counters[C_EDGE_NEXT], 1ull);

@@ -794,6 +794,7 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
     if (input_failed(a.status)) return;
     uint32_t *map = a.maps + (size_t)blockIdx.x * (size_t)a.n * L;
     uint64_t count = a.counters[a.count_idx];
+    if (blockIdx.x >= count) return;  // more workgroups than tasks
     if (tid == 0) s_mc = map_classes(a);
     __syncthreads();
     while (true) {
