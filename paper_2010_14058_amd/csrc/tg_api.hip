@@ -395,8 +395,12 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // status, counters and global accumulators start at zero
     HIPCHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0, 8, st));
     HIPCHK(launch_fill_u64(counters, 0, C_NUM, st));
-    if (batch) HIPCHK(launch_fill_u64(global_counts, 0, batch->globals_len, st));
-    else HIPCHK(launch_fill_u64(gacc, 0, gw, st));
+    if (!batch) HIPCHK(launch_fill_u64(gacc, 0, gw, st));
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    int cus = 0;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    if (cus < 1) cus = 256;
 
     // ---- input checks: batch descriptor, rows, degrees, edge numbering.
     // Every kernel after a check returns at once once an input check has
@@ -404,9 +408,11 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // later launches (hub core, super-hubs, largest degree).
     uint64_t max_gsize = 0;
     if (batch) {
+        // two lists of graph ids in the space of the edge ranges
+        uint32_t *glist = reinterpret_cast<uint32_t *>(gedge);
         HIPCHK(launch_batch_graphs(batch->node_ptr, batch->gL, batch->goff, batch->G, n, L,
-                                   batch->globals_len, batch->max_nodes, node_graph, status,
-                                   counters + C_MAX_GSIZE, st));
+                                   batch->globals_len, batch->max_nodes, glist, counters, status,
+                                   st));
         if (async) {
             max_gsize = (uint64_t)batch->max_nodes;
         } else {
@@ -417,6 +423,26 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
             HIPCHK(hipStreamSynchronize(st));
             if (bst) return status_from_bits(bst);
         }
+        // only the graphs' global vectors, every graph small: counted graph
+        // by graph in LDS, with no relabelling and no per-edge counts
+        if (!per_edge && small_batch_fits((int64_t)max_gsize, L)) {
+            HIPCHK(launch_small_batch(row_ptr, col, types, n, nnz, *batch, (int)max_gsize, L, cus,
+                                      glist, counters, global_counts, status, st));
+            timing_mark("small");
+            if (async) {
+                HIPCHK(launch_status_code(status, status_out, st));
+                return TG_OK;
+            }
+            uint32_t end_bits = 0;
+            HIPCHK(hipMemcpyAsync(&end_bits, status, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            memset(g_timing.stats, 0, sizeof(g_timing.stats));
+            return status_from_bits(end_bits);
+        }
+        // the list lengths share their counters with the 4-cycle groups
+        HIPCHK(launch_fill_u64(counters, 0, C_B_HEAVY, st));
+        HIPCHK(launch_batch_nodes(batch->node_ptr, batch->G, node_graph, status, st));
+        HIPCHK(launch_fill_u64(global_counts, 0, batch->globals_len, st));
     }
     HIPCHK(launch_check_rows(row_ptr, col, types, n, nnz, L, deg, ucount, status, node_graph,
                              batch ? batch->gL : nullptr, st));
@@ -545,15 +571,11 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     ca.blk_flag = nullptr;
     ca.hub_ids = 0;
     ca.max_deg = max_deg;
-    int dev = 0;
-    HIPCHK(hipGetDevice(&dev));
-    int cus = 0;
-    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     // light groups differ in size up to 512 wedges: many small workgroups
     // balance them (each clears its LDS map per group anyway).  There is at
     // most one group per node: a grid of 262,144 workgroups that find no
     // group costs 0.23 ms per pass (a graph of 20 nodes), 6 us sized by n
-    int64_t light_wgs = (int64_t)(cus > 0 ? cus : 256) * 1024;
+    int64_t light_wgs = (int64_t)cus * 1024;
     if (light_wgs > n) light_wgs = n;
     const unsigned light_grid = (unsigned)light_wgs;
     // a heavy group has more wedges than the light bucket: none can exist
@@ -663,7 +685,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // kernel far better than a few long grid-stride loops, except where each
     // workgroup ends by flushing a whole global histogram (fused, one graph)
     const int64_t per_cu = (xyk || batch) ? 2048 : 24;
-    unsigned edge_grid = (unsigned)((cus > 0 ? cus : 256) * per_cu);
+    unsigned edge_grid = (unsigned)(cus * per_cu);
     int64_t units = batch ? (m + BATCH_EDGE_CHUNK - 1) / BATCH_EDGE_CHUNK : m;
     if ((int64_t)edge_grid > units) edge_grid = (unsigned)(units > 0 ? units : 1);
     HIPCHK(launch_edges(false, ea, edge_grid, st));
@@ -684,13 +706,13 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         ed.gacc = pacc;
         ed.gw = (int)pl.gstart[9];
         ed.hist_in_lds = (size_t)ed.gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
-        HIPCHK(launch_derive_pa(ed, pl, (unsigned)(cus > 0 ? cus * 8 : 2048), st));
+        HIPCHK(launch_derive_pa(ed, pl, (unsigned)(cus * 8), st));
         timing_mark("derive");
         if (global_counts) HIPCHK(launch_pa_finalize(pacc, pl, global_counts, status, st));
         timing_mark("global");
     } else if (xyk) {
         ed.hist_in_lds = (size_t)gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
-        HIPCHK(launch_derive(ed, (unsigned)(cus > 0 ? cus * 8 : 2048), st));
+        HIPCHK(launch_derive(ed, (unsigned)(cus * 8), st));
         timing_mark("derive");
     }
     if (pa) {

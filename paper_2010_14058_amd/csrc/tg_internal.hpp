@@ -69,6 +69,15 @@ constexpr int64_t BLK_MIN_WEDGES_B = int64_t(1) << 31;
 constexpr int64_t HUB_LDS_BYTES = 20480;   // default LDS for the pass-B kernel's hub targets
 constexpr size_t BLK_BUDGET = size_t(4) << 30;  // default bytes of records
 
+// Batches of graphs of at most this many nodes are counted graph by graph in
+// LDS when only global counts are asked for (tg_small.hip): 512 rows of 512
+// bits take 37 KB.
+constexpr int SMALL_NODES = 512;
+// Size classes: up to 128 nodes (27 KB of LDS with eight types and 256
+// threads), up to 256 nodes (45 KB with 512 threads), up to 512 nodes (103 KB
+// with 1024 threads).
+constexpr int SMALL_LO = 128, SMALL_MID = 256;
+
 // Device-side layout of everything the library keeps in the caller's
 // workspace.  All offsets are byte offsets from the workspace base.
 struct Layout {
@@ -264,6 +273,13 @@ struct EdgeArgs {
     int64_t G;
 };
 
+// Batches of small graphs, global counts only (tg_small.hip).
+bool small_batch_fits(int64_t max_nodes, int L_max);
+hipError_t launch_small_batch(const int64_t *rp, const int32_t *col, const uint8_t *types,
+                              int64_t n, int64_t nnz, const BatchIn &b, int max_nodes, int L_max,
+                              int cus, const uint32_t *list, uint64_t *counters, uint64_t *out,
+                              uint32_t *status, hipStream_t st);
+
 // Position-aware rows (tg_position.hip): blocks in row order; a block is L
 // wide (3-node), L^2 (ordered role pairs) or L(L+1)/2 (unordered pairs).
 enum PaBlock {
@@ -312,8 +328,10 @@ hipError_t launch_check_edge_count(const int64_t *eoff, int64_t n, int64_t m, ui
 hipError_t launch_status_code(const uint32_t *status, int32_t *out, hipStream_t st);
 hipError_t launch_batch_graphs(const int64_t *node_ptr, const int32_t *gL, const int64_t *goff,
                                int64_t G, int64_t n, int L_max, int64_t globals_len,
-                               int64_t max_nodes, int32_t *node_graph, uint32_t *status,
-                               uint64_t *max_gsize, hipStream_t st);
+                               int64_t max_nodes, uint32_t *list, uint64_t *counters,
+                               uint32_t *status, hipStream_t st);
+hipError_t launch_batch_nodes(const int64_t *node_ptr, int64_t G, int32_t *node_graph,
+                              const uint32_t *status, hipStream_t st);
 hipError_t launch_batch_edges(const int64_t *node_ptr, const int64_t *eoff, int64_t G,
                               int64_t *gedge_ptr, const uint32_t *status, hipStream_t st);
 hipError_t launch_batch_finalize(uint64_t *globals, const int32_t *gL, const int64_t *goff, int64_t G,
