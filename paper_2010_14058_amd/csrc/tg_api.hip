@@ -122,6 +122,7 @@ tg_status plan_layout(int64_t n, int64_t nnz, int L, Layout *lay, int64_t G, con
     };
     y.off_status = take(64);
     y.off_counters = take(sizeof(uint64_t) * C_NUM);
+    y.off_gacc = take(sizeof(uint64_t) * gw);
     y.off_deg = take(sizeof(uint32_t) * (n + 1));
     y.off_ucount = take(sizeof(int64_t) * (n + 1));
     y.off_eoff = take(sizeof(int64_t) * (n + 1));
@@ -153,7 +154,6 @@ tg_status plan_layout(int64_t n, int64_t nnz, int L, Layout *lay, int64_t G, con
     y.off_list_edge = take(sizeof(uint32_t) * (y.m + 1));
     y.off_maps = take(per_map * (size_t)y.heavy_slots);
     y.off_tbuf = take(per_t * (size_t)y.heavy_edge_slots);
-    y.off_gacc = take(sizeof(uint64_t) * gw);
     y.off_sort_tmp = take(y.sort_tmp_bytes);
     y.off_hstart = take(sizeof(int64_t) * (n + 1));
     y.off_eslot = take(sizeof(uint32_t) * (2 * y.m + 1));
@@ -334,6 +334,21 @@ static T *at(void *base, size_t off) {
     return reinterpret_cast<T *>(static_cast<char *>(base) + off);
 }
 
+// Whether the calling thread's scheduling knobs are the defaults (the scratch
+// budgets aside, which only bound memory).
+static bool knobs_default() {
+    static const struct { int knob; int64_t value; } want[] = {
+        {TG_TUNE_TASK_WEDGES, TASK_WEDGES},     {TG_TUNE_CLEAR_BYTES, SEQ_CLEAR_BYTES},
+        {TG_TUNE_RANGE_BYTES, TASK_RANGE_BYTES}, {TG_TUNE_DERIVE_EDGES, 0},
+        {TG_TUNE_LIGHT_WEDGES, LIGHT_MAXW},     {TG_TUNE_EDGE_DEG, TCAP},
+        {TG_TUNE_SH_MAX, SH_MAX},               {TG_TUNE_SH_DEG, SH_DMIN},
+        {TG_TUNE_BLK_WEDGES, BLK_MIN_WEDGES},   {TG_TUNE_BLK_TASK, BLK_TASK},
+        {TG_TUNE_BLK_WEDGES_B, BLK_MIN_WEDGES_B}, {TG_TUNE_HUB_LDS, HUB_LDS_BYTES}};
+    for (const auto &w : want)
+        if (g_tune[w.knob] != w.value) return false;
+    return true;
+}
+
 // One counting call.  pa: per_edge and global_counts receive the
 // position-aware layout (needs the separate derivation pass, y.defer).
 // status_out (batches only): the call does not synchronise with the host at
@@ -392,15 +407,41 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
 
     timing_reset(st);
     timing_mark("start");
-    // status, counters and global accumulators start at zero
-    HIPCHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0, 8, st));
-    HIPCHK(launch_fill_u64(counters, 0, C_NUM, st));
-    if (!batch) HIPCHK(launch_fill_u64(gacc, 0, gw, st));
+    // status, counters and global accumulators (consecutive) start at zero
+    HIPCHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0,
+                           (int64_t)((y.off_gacc - y.off_status) / sizeof(uint64_t)) + gw, st));
     int dev = 0;
     HIPCHK(hipGetDevice(&dev));
     int cus = 0;
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (cus < 1) cus = 256;
+
+    // ---- few edges: each counted from its own neighbourhood.  The kernels
+    // themselves measure the walk and leave it to the general pipeline below
+    // when it is too long; a caller who set scheduling knobs wants that
+    // pipeline's kernels.
+    if (!batch && !pa && direct_fits(n, m) && knobs_default()) {
+        // copies of the global sums in the 4-cycle maps' space, else the one
+        // accumulator
+        const int64_t map_words = (int64_t)y.heavy_slots * n * L / 2;
+        HIPCHK(launch_direct(row_ptr, col, types, n, nnz, L, gw, ucount,
+                             reinterpret_cast<uint32_t *>(eoff), per_edge,
+                             map_words >= gw ? reinterpret_cast<uint64_t *>(maps) : gacc,
+                             map_words >= gw ? map_words : gw, global_counts, counters, status, cus,
+                             st));
+        timing_mark("direct");
+        uint64_t head[64 / sizeof(uint64_t) + C_NUM + 32];
+        const size_t bytes = y.off_counters - y.off_status + sizeof(uint64_t) * C_NUM;
+        if (bytes > sizeof(head)) return TG_E_INTERNAL;
+        HIPCHK(hipMemcpyAsync(head, status, bytes, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        const uint32_t bits_now = (uint32_t)head[0];
+        if (bits_now) return status_from_bits(bits_now);
+        if (head[(y.off_counters - y.off_status) / sizeof(uint64_t) + C_DIRECT_ON]) {
+            memset(g_timing.stats, 0, sizeof(g_timing.stats));
+            return TG_OK;
+        }
+    }
 
     // ---- input checks: batch descriptor, rows, degrees, edge numbering.
     // Every kernel after a check returns at once once an input check has

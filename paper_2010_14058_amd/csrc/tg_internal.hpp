@@ -69,6 +69,14 @@ constexpr int64_t BLK_MIN_WEDGES_B = int64_t(1) << 31;
 constexpr int64_t HUB_LDS_BYTES = 20480;   // default LDS for the pass-B kernel's hub targets
 constexpr size_t BLK_BUDGET = size_t(4) << 30;  // default bytes of records
 
+// Single graphs counted edge by edge from their own neighbourhoods
+// (tg_direct.hip): at most this many nodes (their marks fit LDS), edges,
+// largest degree (the near nodes of one edge fit LDS) and walk steps.
+constexpr int64_t DIRECT_NODES = 8192;
+constexpr int64_t DIRECT_EDGES = 1 << 16;
+constexpr int DIRECT_DEG = 512;
+constexpr uint64_t DIRECT_STEPS = uint64_t(1) << 27;
+
 // Batches of graphs of at most this many nodes are counted graph by graph in
 // LDS when only global counts are asked for (tg_small.hip): 512 rows of 512
 // bits take 37 KB.
@@ -125,7 +133,8 @@ enum Counter {
     C_BLK_MAT,                              // 1: this pass's histogram rows are in the matrix
     C_BLK_NEXT_E,                           // eight emit queues, one per XCD
     C_BLK_NEXT_E_END = C_BLK_NEXT_E + 8,
-    C_NUM = C_BLK_NEXT_E_END
+    C_DIRECT_STEPS = C_BLK_NEXT_E_END, C_DIRECT_DEG, C_DIRECT_ON,
+    C_NUM
 };
 
 // Workspace budgets of the per-workgroup scratch regions: the heavy 4-cycle
@@ -272,6 +281,14 @@ struct EdgeArgs {
     const int64_t *goff;         // [G+1]
     int64_t G;
 };
+
+// Single graphs of few edges (tg_direct.hip).
+bool direct_fits(int64_t n, int64_t m);
+hipError_t launch_direct(const int64_t *rp, const int32_t *col, const uint8_t *types, int64_t n,
+                         int64_t nnz, int L, int gw, int64_t *ucount, uint32_t *eoff,
+                         uint64_t *rows, uint64_t *sums, int64_t sum_words,
+                         uint64_t *global_counts, uint64_t *counters, uint32_t *status, int cus,
+                         hipStream_t st);
 
 // Batches of small graphs, global counts only (tg_small.hip).
 bool small_batch_fits(int64_t max_nodes, int L_max);
