@@ -556,7 +556,8 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     timing_mark("prep");
 
     // ---- typed triangles and node aggregates
-    HIPCHK(launch_tri(nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, counters + C_TRI_SUM,
+    uint32_t *ttot = val_a;   // free once the relabelled CSR stands
+    HIPCHK(launch_tri(nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, ttot, counters + C_TRI_SUM,
                       sh_base, nw, SB, hub_base, Hw, HB, status, st));
     timing_mark("tri");
     // every degree below 2^16: node aggregates, per-edge 4-cycle counts and
@@ -680,7 +681,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     EdgeArgs ea;
     ea.nrp = nrp; ea.ncol = ncol; ea.ntype = ntype; ea.neid = neid; ea.ei = ei; ea.ej = ej;
     ea.ctype = ctype;
-    ea.tri = tri; ea.tdeg = tdeg; ea.tri_slot = tri_slot; ea.A = A; ea.D = D; ea.NC = NC; ea.m = m; ea.L = L;
+    ea.tri = tri; ea.ttot = ttot; ea.tdeg = tdeg; ea.tri_slot = tri_slot; ea.A = A; ea.D = D; ea.NC = NC; ea.m = m; ea.L = L;
     ea.agg_u32 = words32 ? 1 : 0;  // A, D and NC entries below 2^32
     ea.rows = per_edge; ea.gacc = gacc; ea.gw = gw;
     ea.hist_in_lds = (size_t)gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
@@ -727,8 +728,15 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // workgroup ends by flushing a whole global histogram (fused, one graph)
     const int64_t per_cu = (xyk || batch) ? 2048 : 24;
     unsigned edge_grid = (unsigned)(cus * per_cu);
+    // the eight-lane kernel's sums are 32-bit and kept for the separate
+    // derivation
+    ea.few_max = xyk && words32 ? FEW_MAX : 0;
+    ea.few_list = val_b;
+    ea.light_list = le + (m > 0 ? m - 1 : 0);
     int64_t units = batch ? (m + BATCH_EDGE_CHUNK - 1) / BATCH_EDGE_CHUNK : m;
     if ((int64_t)edge_grid > units) edge_grid = (unsigned)(units > 0 ? units : 1);
+    if (xyk && m > 0) HIPCHK(launch_edge_classes(ea, cus, st));
+    if (ea.few_max > 0 && m > 0) HIPCHK(launch_edges_few(ea, edge_grid, st));
     HIPCHK(launch_edges(false, ea, edge_grid, st));
     timing_mark("edges_light");
     EdgeArgs eh = ea;

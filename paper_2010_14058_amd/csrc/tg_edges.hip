@@ -779,15 +779,19 @@ __device__ __forceinline__ void derive_pair(const EdgeArgs &a, int64_t e, int32_
         const int h = o <= 4 ? 3 : o == 5 ? 4 : o == 6 ? 5 : o <= 9 ? 6 : o <= 11 ? 7 : 8;
         hist_add(a, hist, hbase + (h - 3) * n4 + r4, (uint64_t)v, gid);
     };
+    // rows of types without a triangle are zero (and unwritten for an edge
+    // with no triangle at all)
+    auto rt = [&](const XT *q) { return nTt ? (int64_t)q[qa] : (int64_t)0; };
+    auto ru = [&](const XT *q) { return nTu ? (int64_t)q[qb] : (int64_t)0; };
     // cliques and chordal cycles
-    const int64_t K0 = (int64_t)K[qa], K1 = (int64_t)K[qb];
+    const int64_t K0 = rt(K), K1 = ru(K);
     if (same && (K0 & 1)) bad |= ST_INTERNAL;
     if (!same && K0 != K1) bad |= ST_INTERNAL;
     const int64_t g12 = same ? K0 / 2 : K0;
     emit(12, g12);
     emit(11, (same ? nTt * (nTt - 1) / 2 : nTt * nTu) - g12);                 // Lemma 4
-    const int64_t Xi0 = (int64_t)Xi[qa], Xi1 = (int64_t)Xi[qb];
-    const int64_t Xj0 = (int64_t)Xj[qa], Xj1 = (int64_t)Xj[qb];
+    const int64_t Xi0 = rt(Xi), Xi1 = ru(Xi);
+    const int64_t Xj0 = rt(Xj), Xj1 = ru(Xj);
     // C_i(x,y): pairs k in T^x, r in S_i^y adjacent; likewise C_j
     const int64_t Ci0 = Xi0 - nTt * (tb == u) - K0, Ci1 = Xi1 - nTu * (tb == t) - K1;
     const int64_t Cj0 = Xj0 - nTt * (ta == u) - K0, Cj1 = Xj1 - nTu * (ta == t) - K1;
@@ -813,7 +817,7 @@ __device__ __forceinline__ void derive_pair(const EdgeArgs &a, int64_t e, int32_
     emit(7, g7);
     emit(5, (same ? Sit * (Sit - 1) / 2 + Sjt * (Sjt - 1) / 2 : Sit * Siu + Sjt * Sju) - g7);  // Lemma 2
     // 4-path end edges: neighbours of S_i / S_j outside the edge's sets
-    const int64_t Y0 = (int64_t)Y[qa], Y1 = (int64_t)Y[qb];
+    const int64_t Y0 = rt(Y), Y1 = ru(Y);
     const int64_t dli0 = (int64_t)Di[qa] - Y0 - (tb == t) * (int64_t)dj[u];
     const int64_t dli1 = (int64_t)Di[qb] - Y1 - (tb == u) * (int64_t)dj[t];
     const int64_t dlj0 = (int64_t)Dj[qa] - Y0 - (ta == t) * (int64_t)di[u];
@@ -879,6 +883,70 @@ __device__ __forceinline__ EdgeShared carve(const EdgeArgs &a, uint64_t *sm, uin
     return S;
 }
 
+// Class of an edge: by its smaller degree (heavy above tcap), then by its
+// triangles.  Without a triangle its Xi, Xj, Y and K are zero and nobody
+// touches them: 32 % of the edges of the 10M-edge power law, 66 % of the
+// tripartite graph's, 71 % of a 1M-edge request's.
+enum EdgeClass { EDGE_NONE, EDGE_FEW, EDGE_LIGHT, EDGE_HEAVY };
+
+__device__ __forceinline__ int edge_class(const EdgeArgs &a, int64_t e) {
+    const int32_t i = a.ei[e], j = a.ej[e];
+    const int64_t di = a.nrp[i + 1] - a.nrp[i], dj = a.nrp[j + 1] - a.nrp[j];
+    const int64_t d = di < dj ? di : dj;
+    if (d > a.tcap) return EDGE_HEAVY;
+    const uint32_t t = a.ttot[e];
+    if (!t) return EDGE_NONE;
+    return (int64_t)t <= a.few_max && d <= FEW_DEG ? EDGE_FEW : EDGE_LIGHT;
+}
+
+// Lists of the edges of each class (separate derivation): few and heavy edges
+// from the front of their lists, light ones from the back of the heavy list.
+// One atomic per class and workgroup.  The lists keep a hub's edges, which are
+// consecutive, on different waves: a wave that took 64 consecutive edges itself
+// worked through a hub's edges one after the other (a 1M-edge power law's
+// light edges went from 2.9 to 5.8 ms).
+constexpr int CLASS_THREADS = 1024;
+
+__global__ void __launch_bounds__(CLASS_THREADS) k_edge_classes(EdgeArgs a) {
+    __shared__ uint32_t cnt[3][CLASS_THREADS / WAVE];
+    __shared__ unsigned long long base[3];
+    if (input_failed(a.status)) return;
+    const int lane = lane_id(), w = threadIdx.x / WAVE;
+    for (int64_t e0 = (int64_t)blockIdx.x * CLASS_THREADS; e0 < a.m;
+         e0 += (int64_t)gridDim.x * CLASS_THREADS) {
+        const int64_t e = e0 + threadIdx.x;
+        const int c = e < a.m ? edge_class(a, e) : EDGE_NONE;
+        uint64_t bal[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            bal[q] = __ballot(c == EDGE_FEW + q);
+            if (lane == 0) cnt[q][w] = (uint32_t)__popcll(bal[q]);
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            uint32_t run = 0;
+            for (int x = 0; x < CLASS_THREADS / WAVE; ++x) {
+                const uint32_t k = cnt[threadIdx.x][x];
+                cnt[threadIdx.x][x] = run;
+                run += k;
+            }
+            const int which = threadIdx.x == 0 ? C_EDGE_FEW : threadIdx.x == 1 ? C_EDGE_LIGHT : C_EDGE_HEAVY;
+            base[threadIdx.x] =
+                run ? atomicAdd((unsigned long long *)&a.counters[which], (unsigned long long)run) : 0ull;
+        }
+        __syncthreads();
+        if (c != EDGE_NONE) {
+            const int q = c - EDGE_FEW;
+            const uint64_t b = q == 0 ? bal[0] : q == 1 ? bal[1] : bal[2];
+            const int64_t at = (int64_t)(base[q] + cnt[q][w] + __popcll(b & ((1ull << lane) - 1ull)));
+            if (q == 0) a.few_list[at] = (uint32_t)e;
+            else if (q == 1) a.light_list[-at] = (uint32_t)e;
+            else a.heavy_list[at] = (uint32_t)e;
+        }
+        __syncthreads();
+    }
+}
+
 // Light edges: one wave per edge (|T| <= min degree <= tcap, lists in LDS).
 // DEFER: the edge's Xi, Xj, Y, K go to a.xyk and k_derive does the rest, so
 // this kernel carries no derivation state (fewer registers, more waves).
@@ -908,24 +976,20 @@ __device__ __forceinline__ void edges_light_body(const EdgeArgs &a) {
     __shared__ int64_t slot_e[4];
     __shared__ int32_t slot_i[4], slot_j[4];
     int nb = 0;  // edges waiting for their derivation
-    // build T, the gathers and the cliques of edge e into derive slot nb;
-    // edges of the heavy path are queued instead
+    // build T, the gathers and the cliques of edge e into derive slot nb
     auto one_edge = [&](int64_t e) {
-        int32_t i = a.ei[e], j = a.ej[e];
-        int64_t di = a.nrp[i + 1] - a.nrp[i], dj = a.nrp[j + 1] - a.nrp[j];
-        if ((di < dj ? di : dj) > a.tcap) {
-            if (lane == 0)
-                a.heavy_list[atomicAdd((unsigned long long *)&a.counters[C_EDGE_HEAVY], 1ull)] =
-                    (uint32_t)e;
-            return;
-        }
+        const int32_t i = a.ei[e], j = a.ej[e];
         EdgeShared Sb = S;
         Sb.Xi = S.Xi + (size_t)nb * 4 * LL;
         Sb.Xj = Sb.Xi + LL;
         Sb.Y = Sb.Xi + 2 * LL;
         Sb.K = Sb.Xi + 3 * LL;
-        edge_build<WAVE>(a, i, j, Sb, lane);
-        edge_cliques<WAVE>(a, i, j, Sb, a.TM, F, lane);
+        if (DEFER || a.ttot[e]) {
+            edge_build<WAVE>(a, i, j, Sb, lane);
+            edge_cliques<WAVE>(a, i, j, Sb, a.TM, F, lane);
+        } else {
+            for (int q = lane; q < 4 * LL; q += WAVE) Sb.Xi[q] = 0;
+        }
         if constexpr (DEFER) {
             store_xyk(a, e, Sb.Xi, lane, WAVE);
             return;
@@ -945,10 +1009,38 @@ __device__ __forceinline__ void edges_light_body(const EdgeArgs &a) {
         __syncthreads();
         nb = 0;
     };
-    if (!a.batch) {
-        for (int64_t e = blockIdx.x; e < a.m; e += gridDim.x) {
-            one_edge(e);
-            if (nb == EB) derive_all();
+    // fused derivation: bit mask of the edges e0 + lane, e0 + lane < e1, that
+    // this kernel takes; edges of the heavy path are queued
+    auto classify = [&](int64_t e0, int64_t e1) {
+        const int64_t e = e0 + lane;
+        bool mine = false, heavy = false;
+        if (e < e1) {
+            heavy = edge_class(a, e) == EDGE_HEAVY;
+            mine = !heavy;
+        }
+        const uint64_t hv = __ballot(heavy);
+        if (hv) {
+            uint64_t at = 0;
+            if (lane == 0)
+                at = atomicAdd((unsigned long long *)&a.counters[C_EDGE_HEAVY],
+                               (unsigned long long)__popcll(hv));
+            at = __shfl((unsigned long long)at, 0, WAVE);
+            if (heavy) a.heavy_list[at + __popcll(hv & ((1ull << lane) - 1ull))] = (uint32_t)e;
+        }
+        return (uint64_t)__ballot(mine);
+    };
+    if constexpr (DEFER) {
+        const uint64_t count = a.counters[C_EDGE_LIGHT];
+        for (uint64_t q = blockIdx.x; q < count; q += gridDim.x) one_edge(a.light_list[-(int64_t)q]);
+    } else if (!a.batch) {
+        for (int64_t e0 = (int64_t)blockIdx.x * 8; e0 < a.m; e0 += (int64_t)gridDim.x * 8) {
+            uint64_t mask = classify(e0, e0 + 8 < a.m ? e0 + 8 : a.m);
+            while (mask) {
+                const int b = __ffsll((long long)mask) - 1;
+                mask &= mask - 1;
+                one_edge(e0 + b);
+                if (nb == EB) derive_all();
+            }
         }
         derive_all();
         if (a.hist_in_lds)
@@ -978,20 +1070,142 @@ __device__ __forceinline__ void edges_light_body(const EdgeArgs &a) {
             int64_t e0 = c * BATCH_EDGE_CHUNK;
             int64_t e1 = e0 + BATCH_EDGE_CHUNK < a.m ? e0 + BATCH_EDGE_CHUNK : a.m;
             int64_t cur = a.ngraph[a.ei[e0]];
-            for (int64_t e = e0; e < e1; ++e) {
-                int64_t g = a.ngraph[a.ei[e]];
-                if (g != cur) {
-                    flush(cur);
-                    cur = g;
+            for (int64_t b0 = e0; b0 < e1; b0 += WAVE) {
+                uint64_t mask = classify(b0, b0 + WAVE < e1 ? b0 + WAVE : e1);
+                while (mask) {
+                    const int64_t e = b0 + __ffsll((long long)mask) - 1;
+                    mask &= mask - 1;
+                    const int64_t g = a.ngraph[a.ei[e]];
+                    if (g != cur) {
+                        flush(cur);
+                        cur = g;
+                    }
+                    one_edge(e);
+                    derive_all();
                 }
-                one_edge(e);
-                derive_all();
             }
             flush(cur);
         }
     }
     bad = wave_or(bad);
     if (lane == 0 && bad) atomicOr(a.status, bad);
+}
+
+// Edges of few triangles (at most FEW_MAX, smaller degree at most FEW_DEG),
+// eight lanes each.  A wave per edge spends such an edge on
+// a chain of about ten dependent loads with most lanes idle.  The shorter row
+// is walked from its end (the members of a triangle set are mostly high ranks)
+// until all triangles are found; each lane then owns columns of the gathers,
+// and the member pairs are tested for adjacency.  On the 10M-edge power law
+// 4.5M edges take 2.3 ms; with them and the edges without a triangle taken out
+// the one-wave kernel went from 32 to 20.6 ms, on the tripartite graph (5M
+// edges) the two from 6.4 to 1.1 ms, on a 1M-edge request from 1.5 to 0.55 ms.
+constexpr int FEW_LANES = 8;
+constexpr int FEW_GROUPS = WAVE / FEW_LANES;
+
+__global__ void __launch_bounds__(WAVE) k_edges_few(EdgeArgs a) {
+    extern __shared__ uint32_t sm_few[];
+    if (input_failed(a.status)) return;
+    const int lane = threadIdx.x, grp = lane / FEW_LANES, gl = lane % FEW_LANES;
+    const int L = a.L, LL = L * L, LP = tri_pitch(L);
+    // per group: Xi, Xj, Y, K, then the members' ids, slots at i and at j, types
+    uint32_t *acc = sm_few + (size_t)grp * (4 * LL + 4 * FEW_MAX);
+    uint32_t *mem = acc + 4 * LL, *msi = mem + FEW_MAX, *msj = msi + FEW_MAX, *mty = msj + FEW_MAX;
+    uint32_t *out = reinterpret_cast<uint32_t *>(a.xyk);
+    const uint64_t count = a.counters[C_EDGE_FEW];
+    for (uint64_t q0 = (uint64_t)blockIdx.x * FEW_GROUPS; q0 < count;
+         q0 += (uint64_t)gridDim.x * FEW_GROUPS) {
+        const bool on = q0 + grp < count;
+        const int64_t e = on ? a.few_list[q0 + grp] : 0;
+        int want = 0, cnt = 0;
+        if (on) {
+            const int32_t i = a.ei[e], j = a.ej[e];
+            want = (int)a.ttot[e];
+            int64_t sb = a.nrp[i], se = a.nrp[i + 1], bb = a.nrp[j], be = a.nrp[j + 1];
+            const bool i_small = se - sb <= be - bb;
+            if (!i_small) {
+                const int64_t t0 = sb, t1 = se;
+                sb = bb; se = be; bb = t0; be = t1;
+            }
+            const int32_t big = i_small ? j : i;
+            const bool probe = big >= a.sh_base, big_hub = big >= a.hub_base;
+            const int sidx = big - a.sh_base, hidx = big - a.hub_base;
+            for (int q = gl; q < 4 * LL; q += FEW_LANES) acc[q] = 0u;
+            for (int64_t p0 = se - 1; p0 >= sb && cnt < want; p0 -= FEW_LANES) {
+                const int64_t p = p0 - gl;
+                bool found = false;
+                int32_t x = 0;
+                int64_t q = 0;
+                if (p >= sb) {
+                    x = a.ncol[p];
+                    if (probe) {
+                        found = sh_bit(a.SB, a.nw, sidx, x);
+                        if (found) q = sh_slot(a.SB, a.SP, a.nw, bb, sidx, x);
+                    } else if (big_hub && x >= a.hub_base) {
+                        found = hub_adj(a, hidx, x - a.hub_base);
+                        if (found) q = hub_slot(a, big, hidx, x - a.hub_base);
+                    } else {
+                        q = lower_bound(a.ncol, bb, be, x);
+                        found = q < be && a.ncol[q] == x;
+                    }
+                }
+                const uint32_t hits =
+                    (uint32_t)(__ballot(found) >> (grp * FEW_LANES)) & ((1u << FEW_LANES) - 1u);
+                const int pos = cnt + __popc(hits & ((1u << gl) - 1u));
+                if (found && pos < FEW_MAX) {
+                    mem[pos] = (uint32_t)x;
+                    msi[pos] = (uint32_t)(i_small ? p : q);
+                    msj[pos] = (uint32_t)(i_small ? q : p);
+                    mty[pos] = a.ctype[p];
+                }
+                cnt += __popc(hits);
+            }
+            if (cnt != want) {
+                if (gl == 0) atomicOr(a.status, ST_INTERNAL);
+                if (cnt > want) cnt = want;
+            }
+        }
+        wave_sync();
+        // gathers: lane gl owns columns gl, gl + 8 of every row
+        for (int t2 = gl; t2 < L; t2 += FEW_LANES) {
+#pragma unroll 4
+            for (int k = 0; k < cnt; ++k) {
+                const uint32_t xi = a.tri_slot[(size_t)msi[k] * LP + t2];
+                const uint32_t xj = a.tri_slot[(size_t)msj[k] * LP + t2];
+                const uint32_t yk = a.tdeg[(size_t)mem[k] * LP + t2];
+                uint32_t *row = acc + mty[k] * L + t2;
+                row[0] += xi;
+                row[LL] += xj;
+                row[2 * LL] += yk;
+            }
+        }
+        // clique pairs: member ids fall with their index
+        const int pairs = cnt * (cnt - 1) / 2;
+        for (int f = gl; f < pairs; f += FEW_LANES) {
+            int hi = 1;
+            while (hi * (hi + 1) / 2 <= f) ++hi;   // f = hi (hi - 1) / 2 + lo, lo < hi
+            const int lo = f - hi * (hi - 1) / 2;
+            const int32_t x = (int32_t)mem[hi], y = (int32_t)mem[lo];   // x < y
+            bool adj;
+            if (x >= a.hub_base) adj = hub_adj(a, x - a.hub_base, y - a.hub_base);
+            else if (y >= a.sh_base) adj = sh_bit(a.SB, a.nw, y - a.sh_base, x);
+            else {
+                const int64_t xe = a.nrp[x + 1];
+                const int64_t q = lower_bound(a.ncol, a.nrp[x] + a.nlow[x], xe, y);
+                adj = q < xe && a.ncol[q] == y;
+            }
+            if (!adj) continue;
+            const int tx = mty[hi], ty = mty[lo];
+            atomicAdd(&acc[3 * LL + tx * L + ty], 1u);
+            atomicAdd(&acc[3 * LL + ty * L + tx], 1u);
+        }
+        wave_sync();
+        if (on) {
+            uint32_t *dst = out + (size_t)e * 4 * LL;
+            for (int q = gl; q < 4 * LL; q += FEW_LANES) dst[q] = acc[q];
+        }
+        wave_sync();
+    }
 }
 
 // The deferred variant holds no derivation state; a register budget for six
@@ -1058,6 +1272,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 0 || MODE == 3 ? 5 : 1))) k_edges_hea
         if (idx >= count) break;
         int64_t e = a.heavy_list[idx];
         int32_t i = a.ei[e], j = a.ej[e];
+        if ((MODE == 0 || MODE == 3) && !a.ttot[e]) continue;   // nothing to store
         edge_build<NT, MODE == 3>(a, i, j, S, tid);
         __threadfence_block();
         __syncthreads();
@@ -1181,6 +1396,20 @@ hipError_t launch_edges(bool heavy, const EdgeArgs &args, unsigned grid, hipStre
     } else {
         k_edges_light_fused<false><<<grid, 64, sh, st>>>(args);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st) {
+    int64_t grid = (args.m + CLASS_THREADS - 1) / CLASS_THREADS;
+    if (grid > 8 * (int64_t)cus) grid = 8 * (int64_t)cus;
+    k_edge_classes<<<(unsigned)grid, CLASS_THREADS, 0, st>>>(args);
+    return hipGetLastError();
+}
+
+hipError_t launch_edges_few(const EdgeArgs &args, unsigned grid, hipStream_t st) {
+    const int LL = args.L * args.L;
+    const size_t sh = (size_t)FEW_GROUPS * (4 * LL + 4 * FEW_MAX) * sizeof(uint32_t);
+    k_edges_few<<<grid, WAVE, sh, st>>>(args);
     return hipGetLastError();
 }
 

@@ -45,6 +45,8 @@ constexpr int SEQ_CLEAR_BYTES = 64;       // default bytes per wedge below which
 constexpr int64_t TASK_RANGE_BYTES = 0;  // default map-byte bound per task of a dense heavy group (0: off)
 constexpr int TCAP = 1024;            // triangle set kept in LDS by the light edge kernel
 constexpr int EDGE_THREADS_HEAVY = 256;
+constexpr int FEW_MAX = 16;           // most triangles of an edge of the eight-lane kernel
+constexpr int FEW_DEG = 256;          // largest smaller degree of such an edge (its row is walked)
 constexpr int64_t BATCH_EDGE_CHUNK = 256;  // consecutive edges per work item in batches
 constexpr int HUB_DMIN = 32;          // smallest degree of a hub-core node
 constexpr int HUB_MAX = 8192;         // largest hub core (bit-matrix HUB_MAX^2 bits)
@@ -134,6 +136,7 @@ enum Counter {
     C_BLK_NEXT_E,                           // eight emit queues, one per XCD
     C_BLK_NEXT_E_END = C_BLK_NEXT_E + 8,
     C_DIRECT_STEPS = C_BLK_NEXT_E_END, C_DIRECT_DEG, C_DIRECT_ON,
+    C_EDGE_FEW, C_EDGE_LIGHT,
     C_NUM
 };
 
@@ -239,6 +242,11 @@ struct EdgeArgs {
     const uint32_t *neid;
     const int32_t *ei, *ej;
     const uint32_t *tri;
+    const uint32_t *ttot;        // triangles of each edge, all types
+    int few_max;                 // edges of 1..few_max triangles and smaller degree at most
+                                 // FEW_DEG go to the eight-lane kernel (0: none)
+    uint32_t *few_list;          // their list
+    uint32_t *light_list;        // last entry of the light edges' list, which grows down
     const uint32_t *tdeg;        // typed degrees per node, rows of tri_pitch(L)
     const uint8_t *ctype;        // type of the neighbour at each adjacency slot
     const uint32_t *tri_slot;    // typed triangle counts per slot, rows of tri_pitch(L)
@@ -381,7 +389,7 @@ __host__ __device__ inline int tm_pitch(int L) { return L & ~1; }
 
 hipError_t launch_tri(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype,
                       const int32_t *ei, const int32_t *ej, const uint32_t *eslot,
-                      uint32_t *tri_slot, int64_t m, int L, uint32_t *tri,
+                      uint32_t *tri_slot, int64_t m, int L, uint32_t *tri, uint32_t *ttot,
                       uint64_t *tri_sum, int32_t sh_base, int64_t nw, const uint64_t *SB,
                       int32_t hub_base, int Hw, const uint64_t *HB, const uint32_t *status,
                       hipStream_t st);
@@ -415,6 +423,8 @@ int heavy_chunk_for(int L, int threads, int hub_ids = 0, bool t32 = false);
 int heavy_hub_ids(int L, int64_t n, int64_t bytes);
 hipError_t launch_cycles(int pass, bool heavy, const CycleArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_edges(bool heavy, const EdgeArgs &args, unsigned grid, hipStream_t st);
+hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st);
+hipError_t launch_edges_few(const EdgeArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_derive(const EdgeArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_global_finalize(const uint64_t *gacc, int L, int gw, uint64_t *out,
                                   uint32_t *status, hipStream_t st);

@@ -326,7 +326,8 @@ k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
                       const uint8_t *__restrict__ ctype, const int32_t *__restrict__ ei,
                       const int32_t *__restrict__ ej, const uint32_t *__restrict__ eslot,
                       uint32_t *__restrict__ tri_slot, int64_t m, int L,
-                      uint32_t *__restrict__ tri, uint64_t *__restrict__ tri_sum, int32_t sh_base,
+                      uint32_t *__restrict__ tri, uint32_t *__restrict__ ttot,
+                      uint64_t *__restrict__ tri_sum, int32_t sh_base,
                       int64_t nw, const uint64_t *__restrict__ SB, int32_t hub_base, int Hw,
                       const uint64_t *__restrict__ HB, const uint32_t *__restrict__ status) {
     if (input_failed(status)) return;
@@ -396,6 +397,7 @@ k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
             }
         }
         // one count per group (lanes of a group hold the same totals)
+        if (gl == 0 && e < m) ttot[e] = (uint32_t)tot;
         tot_all += gl == 0 ? tot : 0ull;
     }
     tot_all = wave_sum_u64(tot_all);
@@ -2055,14 +2057,14 @@ hipError_t launch_tdeg(const int64_t *nrp, const int32_t *ncol, const uint8_t *c
 
 hipError_t launch_tri(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype,
                       const int32_t *ei, const int32_t *ej, const uint32_t *eslot,
-                      uint32_t *tri_slot, int64_t m, int L, uint32_t *tri,
+                      uint32_t *tri_slot, int64_t m, int L, uint32_t *tri, uint32_t *ttot,
                       uint64_t *tri_sum, int32_t sh_base, int64_t nw, const uint64_t *SB,
                       int32_t hub_base, int Hw, const uint64_t *HB, const uint32_t *status,
                       hipStream_t st) {
     if (m == 0) return hipSuccess;
     k_tri<<<blocks_bounded(m, 4 * TRI_GROUPS, 32), 256, 0, st>>>(
-        nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, tri_sum, sh_base, nw, SB, hub_base,
-        Hw, HB, status);
+        nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, ttot, tri_sum, sh_base, nw, SB,
+        hub_base, Hw, HB, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }

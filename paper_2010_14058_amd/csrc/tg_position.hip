@@ -128,11 +128,15 @@ __device__ __forceinline__ void pa_pair(const EdgeArgs &a, const PaLayout &pl, c
         if (row) row[pl.start[b] + p] = (uint64_t)v;
         pa_hist_add(a, hist, cls, v);
     };
-    const int64_t K0 = (int64_t)K[qa], K1 = (int64_t)K[qb];
+    // rows of types without a triangle are zero (and unwritten for an edge
+    // with no triangle at all)
+    auto rt = [&](const XT *q) { return nTt ? (int64_t)q[qa] : (int64_t)0; };
+    auto ru = [&](const XT *q) { return nTu ? (int64_t)q[qb] : (int64_t)0; };
+    const int64_t K0 = rt(K), K1 = ru(K);
     if (same && (K0 & 1)) bad |= ST_INTERNAL;
     if (!same && K0 != K1) bad |= ST_INTERNAL;
-    const int64_t Xi0 = (int64_t)Xi[qa], Xi1 = (int64_t)Xi[qb];
-    const int64_t Xj0 = (int64_t)Xj[qa], Xj1 = (int64_t)Xj[qb];
+    const int64_t Xi0 = rt(Xi), Xi1 = ru(Xi);
+    const int64_t Xj0 = rt(Xj), Xj1 = ru(Xj);
     const int64_t Ci0 = Xi0 - nTt * (tb == u) - K0, Ci1 = Xi1 - nTu * (tb == t) - K1;
     const int64_t Cj0 = Xj0 - nTt * (ta == u) - K0, Cj1 = Xj1 - nTu * (ta == t) - K1;
     const int64_t Cyc0 = (int64_t)NC[qa] - Ci1 - Cj0 - K0;
@@ -145,7 +149,7 @@ __device__ __forceinline__ void pa_pair(const EdgeArgs &a, const PaLayout &pl, c
     const int64_t Ej0 = sgj0 - Cj1, Ej1 = sgj1 - Cj0;
     if (same && ((Ei0 & 1) || (Ej0 & 1))) bad |= ST_INTERNAL;
     if (!same && (Ei0 != Ei1 || Ej0 != Ej1)) bad |= ST_INTERNAL;
-    const int64_t Y0 = (int64_t)Y[qa], Y1 = (int64_t)Y[qb];
+    const int64_t Y0 = rt(Y), Y1 = ru(Y);
     const int64_t dli0 = (int64_t)Di[qa] - Y0 - (tb == t) * (int64_t)dj[u];
     const int64_t dli1 = (int64_t)Di[qb] - Y1 - (tb == u) * (int64_t)dj[t];
     const int64_t dlj0 = (int64_t)Dj[qa] - Y0 - (ta == t) * (int64_t)di[u];
