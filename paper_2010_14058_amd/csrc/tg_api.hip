@@ -504,7 +504,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
                           (uint32_t)g_tune[TG_TUNE_SH_DEG], node_graph, ngraph, status, st));
     HIPCHK(launch_excl_scan(ndeg, nrp, n + 1, stmp64, status, st));
     const int bits = bits_for(n);
-    HIPCHK(launch_slot_keys(row_ptr, col, ucount, eoff, newid, n, bits, key_a, val_a, ei, ej, status,
+    HIPCHK(launch_slot_keys(row_ptr, col, ucount, eoff, newid, n, nnz, bits, key_a, val_a, ei, ej, status,
                             st));
     // hub core and super-hubs: single graphs only (in a batch the top ids are
     // not the top degrees); the largest degree sizes the word widths
@@ -527,6 +527,9 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         HIPCHK(hipStreamSynchronize(st));
         if (bits_now) return status_from_bits(bits_now);
     }
+    // rows taken by a workgroup each where others take a wave: the top-ranked
+    // nodes of at least the super-hub degree
+    const int64_t nlong = batch ? 0 : (int64_t)cand[1];
     // hub core: the highest-ranked nodes of degree >= HUB_DMIN, at most HUB_MAX
     const uint64_t hub_cand = batch ? 0 : cand[0], sh_cand = batch ? 0 : cand[1];
     const int H = (int)(hub_cand < (uint64_t)HUB_MAX ? hub_cand : (uint64_t)HUB_MAX);
@@ -550,7 +553,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     uint64_t *HB = at<uint64_t>(ws, y.off_HB);
     uint32_t *hpre = at<uint32_t>(ws, y.off_hpre);
     uint64_t *TM = at<uint64_t>(ws, y.off_TM);
-    HIPCHK(launch_tdeg(nrp, ncol, ctype, n, L, hub_base, tdeg, hstart, nlow, status, st));
+    HIPCHK(launch_tdeg(nrp, ncol, ctype, n, nlong, L, hub_base, tdeg, hstart, nlow, status, st));
     HIPCHK(launch_hub_build(nrp, ncol, hstart, ntype, n, H, Hw, L, HB, hpre, TM, st));
     HIPCHK(launch_superhubs(nrp, ncol, n, S, nw, SB, SP, st));
     timing_mark("prep");
@@ -563,7 +566,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // every degree below 2^16: node aggregates, per-edge 4-cycle counts and
     // derivation inputs stay below 2^32 and are held as 32-bit words
     const bool words32 = max_deg < 65536;
-    HIPCHK(launch_node_aggr(nrp, ncol, ctype, tri_slot, tdeg, n, L, A, D, words32, status, st));
+    HIPCHK(launch_node_aggr(nrp, ncol, ctype, tri_slot, tdeg, n, nlong, L, A, D, words32, status, st));
     timing_mark("aggr");
 
     // ---- 4-cycles from degree-ordered wedges
@@ -590,7 +593,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         HIPCHK(launch_fill_u64(at<uint64_t>(ws, y.off_blk_flag), 0, (2 * (n + 8) + 7) / 8, st));
         HIPCHK(launch_fill_u64(bsel.hist_a, 0, 4 * BLK_BINS, st));
     }
-    HIPCHK(launch_cyc_work(nrp, ncol, neid, eslot, nlow, n, la_l, la_h, lb_l, lb_h, counters,
+    HIPCHK(launch_cyc_work(nrp, ncol, neid, eslot, nlow, n, nlong, la_l, la_h, lb_l, lb_h, counters,
                            (uint64_t)g_tune[TG_TUNE_TASK_WEDGES], L,
                            (uint64_t)g_tune[TG_TUNE_RANGE_BYTES],
                            (uint64_t)g_tune[TG_TUNE_LIGHT_WEDGES], bsel, status, st));

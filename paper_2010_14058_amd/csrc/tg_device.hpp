@@ -120,6 +120,63 @@ static __device__ __forceinline__ int rank4(int a, int b, int c, int d) {
                  binom_small(d + 3, 4));
 }
 
+// Row offsets of the slots [s0, s1) one workgroup takes (flat over the CSR, so
+// that a hub's row is spread over workgroups and short rows fill whole waves).
+constexpr int SLOT_TILE = 2048;
+constexpr int SLOT_ROWS = 1024;
+
+struct SlotTile {
+    int64_t first[SLOT_ROWS + 1];   // offsets of rows r0 .. r1 + 1 when staged
+    int64_t r0, r1;                 // rows holding the first and the last slot
+    int staged;
+};
+
+// Smallest r with rp[r + 1] > key (rp nondecreasing, rp[n] > key), by a wave.
+static __device__ __forceinline__ int64_t slot_search(const int64_t *rp, int64_t n, int64_t key) {
+    int64_t lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int64_t step = (hi - lo + WAVE - 1) / WAVE;
+        const int64_t q = lo + (lane_id() + 1) * step - 1;
+        const int k = __popcll(__ballot(q < hi && rp[q + 1] <= key));
+        lo += k * step;
+        if (lo + step - 1 < hi) hi = lo + step - 1;
+    }
+    return lo;
+}
+
+// Fills T for slots [s0, s1), s0 < s1; by a whole workgroup of at least two waves.
+static __device__ __forceinline__ void slot_tile(const int64_t *rp, int64_t n, int64_t s0,
+                                                 int64_t s1, SlotTile &T) {
+    const int w = threadIdx.x / WAVE;
+    if (w < 2) {
+        const int64_t r = slot_search(rp, n, w == 0 ? s0 : s1 - 1);
+        if (lane_id() == 0) (w == 0 ? T.r0 : T.r1) = r;
+    }
+    __syncthreads();
+    const int64_t rows = T.r1 - T.r0 + 1;
+    if (threadIdx.x == 0) T.staged = rows <= SLOT_ROWS;
+    if (rows <= SLOT_ROWS)
+        for (int64_t q = threadIdx.x; q <= rows; q += blockDim.x) T.first[q] = rp[T.r0 + q];
+    __syncthreads();
+}
+
+// First slot of row u of the tile (u up to r1 + 1).
+static __device__ __forceinline__ int64_t slot_first(const int64_t *rp, const SlotTile &T, int64_t u) {
+    return T.staged ? T.first[u - T.r0] : rp[u];
+}
+
+// Row of slot s, at least u (the row of an earlier slot of the same thread).
+static __device__ __forceinline__ int64_t slot_row(const int64_t *rp, const SlotTile &T, int64_t u,
+                                                   int64_t s) {
+    if (slot_first(rp, T, u + 1) > s) return u;
+    int64_t lo = u + 1, hi = T.r1;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (slot_first(rp, T, mid + 1) <= s) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
 // Super-hub bitmap probes: bit of node x in the bitmap of super-hub index s,
 // and the slot of x inside the super-hub's (sorted) row.
 static __device__ __forceinline__ bool sh_bit(const uint64_t *SB, int64_t nw, int s, int32_t x) {

@@ -34,62 +34,86 @@ namespace {
 // Direction code of a CSR slot relative to its row's node: 0 out, 1 in, 2 both.
 __device__ __forceinline__ int dir_code(uint8_t d) { return d == 1 ? 0 : d == 2 ? 1 : 2; }
 
-// Checks (sorted rows in range, no self-loops, types in range, direction
-// bits 1..3 mirrored by the reverse slot), entries above the diagonal per
-// row, and the direction-split typed degrees deg3[v][t*3 + a].  One wave
-// per row.
+// One thread per row: bounds, type, entries above the diagonal (the row is
+// searched; k_dir_slots checks that it is sorted).
 __global__ void __launch_bounds__(256)
-k_dir_check(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-            const uint8_t *__restrict__ dir, const uint8_t *__restrict__ types, int64_t n,
-            int64_t nnz, int L, int64_t *__restrict__ ucount, uint32_t *__restrict__ deg3,
-            uint32_t *__restrict__ status) {
-    __shared__ uint32_t cnt[256 / WAVE][3 * TG_MAX_L];
-    const int lane = lane_id(), wv = threadIdx.x / WAVE;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ucount[n] = 0;
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv; u < n; u += nwaves) {
-        for (int q = lane; q < 3 * L; q += WAVE) cnt[wv][q] = 0;
-        wave_sync();
+k_dir_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+            const uint8_t *__restrict__ types, int64_t n, int64_t nnz, int L,
+            int64_t *__restrict__ ucount, uint32_t *__restrict__ status) {
+    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    uint32_t bad = 0;
+    if (u < n) {
+        if (u == 0) ucount[n] = 0;
         const int64_t b = rp[u], e = rp[u + 1];
-        uint32_t bad = 0;
-        uint64_t up = 0;
+        int64_t up = 0;
         if (b < 0 || e < b || e > nnz || (u == 0 && b != 0) || (u == n - 1 && e != nnz)) {
             bad = ST_UNSORTED;
         } else {
             if (types[u] >= L) bad |= ST_TYPE_RANGE;
-            for (int64_t s = b + lane; s < e; s += WAVE) {
-                const int32_t x = col[s];
-                if (x < 0 || x >= n) {
-                    bad |= ST_COL_RANGE;
-                    continue;
-                }
-                if (x == u) bad |= ST_SELF_LOOP;
-                if (s > b && col[s - 1] >= x) bad |= ST_UNSORTED;
-                if (x > u) ++up;
-                const uint8_t d = dir[s];
-                const int64_t xb = rp[x], xe = rp[x + 1];
-                if (d == 0 || d > 3 || xb < 0 || xe < xb || xe > nnz) {
-                    bad |= ST_ASYMMETRIC;
-                    continue;
-                }
-                const int64_t r = lower_bound(col, xb, xe, (int32_t)u);
-                const uint8_t want = (uint8_t)(((d & 1) << 1) | (d >> 1));
-                if (r >= xe || col[r] != (int32_t)u || dir[r] != want) bad |= ST_ASYMMETRIC;
-                const int t = types[x];
-                if (t < L) atomicAdd(&cnt[wv][t * 3 + dir_code(d)], 1u);
-                else bad |= ST_TYPE_RANGE;
-            }
+            up = e - upper_bound(col, b, e, (int32_t)u);
         }
-        bad = wave_or(bad);
-        up = wave_sum_u64(up);
-        wave_sync();
-        if (lane == 0) {
-            ucount[u] = bad ? 0 : (int64_t)up;
-            if (bad) atomicOr(status, bad);
-        }
-        for (int q = lane; q < 3 * L; q += WAVE) deg3[(size_t)u * 3 * L + q] = cnt[wv][q];
-        wave_sync();
+        ucount[u] = up;
     }
+    bad = wave_or(bad);
+    if (lane_id() == 0 && bad) atomicOr(status, bad);
+}
+
+// One thread per slot (row bounds and types are valid here): order, range, no
+// self-loops, direction bits 1..3 mirrored by the reverse slot, and the
+// direction-split typed degrees deg3[v][t*3 + a] (zero before), counted in LDS
+// per tile of slots.  A wave per row took 4.3 ms on the 10M-edge power law,
+// half of it for the 53,000-neighbour hub's wave; 2.0 ms here, the searches.
+constexpr int DIR_TILE_WORDS = 4096;
+
+__global__ void __launch_bounds__(256)
+k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+            const uint8_t *__restrict__ dir, const uint8_t *__restrict__ types, int64_t n,
+            int64_t nnz, int L, uint32_t *__restrict__ deg3, uint32_t *__restrict__ status) {
+    __shared__ SlotTile T;
+    __shared__ uint32_t cnt[DIR_TILE_WORDS];
+    if (load_agent(status) != 0) return;
+    const int tid = threadIdx.x, C = 3 * L;
+    uint32_t bad = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
+         s0 += (int64_t)gridDim.x * SLOT_TILE) {
+        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+        slot_tile(rp, n, s0, s1, T);
+        const int64_t words = (T.r1 - T.r0 + 1) * C;
+        const bool in_lds = words <= DIR_TILE_WORDS;
+        if (in_lds)
+            for (int q = tid; q < (int)words; q += 256) cnt[q] = 0u;
+        __syncthreads();
+        int64_t u = T.r0;
+        for (int64_t s = s0 + tid; s < s1; s += 256) {
+            u = slot_row(rp, T, u, s);
+            const int32_t x = col[s];
+            if (x < 0 || x >= n) {
+                bad |= ST_COL_RANGE;
+                continue;
+            }
+            if (x == u) bad |= ST_SELF_LOOP;
+            if (s > slot_first(rp, T, u) && col[s - 1] >= x) bad |= ST_UNSORTED;
+            const uint8_t d = dir[s];
+            if (d == 0 || d > 3) {
+                bad |= ST_ASYMMETRIC;
+                continue;
+            }
+            const int64_t xe = rp[x + 1];
+            const int64_t r = lower_bound(col, rp[x], xe, (int32_t)u);
+            const uint8_t want = (uint8_t)(((d & 1) << 1) | (d >> 1));
+            if (r >= xe || col[r] != (int32_t)u || dir[r] != want) bad |= ST_ASYMMETRIC;
+            const int q = types[x] * 3 + dir_code(d);
+            if (in_lds) atomicAdd(&cnt[(int)(u - T.r0) * C + q], 1u);
+            else atomicAdd(&deg3[(size_t)u * C + q], 1u);
+        }
+        __syncthreads();
+        if (in_lds)
+            for (int q = tid; q < (int)words; q += 256)
+                if (cnt[q]) atomicAdd(&deg3[(size_t)T.r0 * C + q], cnt[q]);
+        __syncthreads();
+    }
+    bad = wave_or(bad);
+    if (lane_id() == 0 && bad) atomicOr(status, bad);
 }
 
 __global__ void k_dir_edge_check(const int64_t *__restrict__ eoff, int64_t n, int64_t m,
@@ -98,19 +122,24 @@ __global__ void k_dir_edge_check(const int64_t *__restrict__ eoff, int64_t n, in
 }
 
 // The canonical edge of each upper slot: esrc[e] = u, eslot[e] = s.
-__global__ void k_dir_edges_of(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-                               const int64_t *__restrict__ eoff, int64_t n,
-                               int32_t *__restrict__ esrc, int64_t *__restrict__ eslot) {
-    const int lane = lane_id();
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; u < n;
-         u += nwaves) {
-        const int64_t e = rp[u + 1], first = e - (eoff[u + 1] - eoff[u]);
-        for (int64_t s = first + lane; s < e; s += WAVE) {
-            const int64_t id = eoff[u] + (s - first);
+__global__ void __launch_bounds__(256)
+k_dir_edges_of(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+               const int64_t *__restrict__ eoff, int64_t n, int64_t nnz,
+               int32_t *__restrict__ esrc, int64_t *__restrict__ eslot) {
+    __shared__ SlotTile T;
+    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
+         s0 += (int64_t)gridDim.x * SLOT_TILE) {
+        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+        slot_tile(rp, n, s0, s1, T);
+        int64_t u = T.r0;
+        for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
+            u = slot_row(rp, T, u, s);
+            if (col[s] <= u) continue;
+            const int64_t id = eoff[u + 1] - (slot_first(rp, T, u + 1) - s);
             esrc[id] = (int32_t)u;
             eslot[id] = s;
         }
+        __syncthreads();
     }
 }
 
@@ -495,6 +524,17 @@ unsigned waves_grid(int64_t items) {
     return b > 0 ? (unsigned)b : 1u;
 }
 
+// Workgroups of the flat slot kernels.
+unsigned slots_grid(int64_t nnz) {
+    const int64_t tiles = (nnz + SLOT_TILE - 1) / SLOT_TILE;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        cus > 0 && tiles > (int64_t)cus * 16)
+        return (unsigned)cus * 16;
+    return tiles > 0 ? (unsigned)tiles : 1u;
+}
+
 }  // namespace
 }  // namespace tg
 
@@ -541,8 +581,14 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
     DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(acc), 0, width, st));
     if (n > 0) {
         ksum_begin(st);
-        k_dir_check<<<waves_grid(n), 256, 0, st>>>(row_ptr, col, dir, types, n, nnz, L, ucount,
-                                                    deg3, status);
+        // typed degrees start at zero (rounded up to whole 8-byte words of
+        // their 256-byte aligned region)
+        DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(deg3), 0, (n * 3 * L + 1) / 2, st));
+        k_dir_nodes<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(row_ptr, col, types, n, nnz, L,
+                                                                 ucount, status);
+        if (nnz > 0)
+            k_dir_slots<<<slots_grid(nnz), 256, 0, st>>>(row_ptr, col, dir, types, n, nnz, L, deg3,
+                                                         status);
         ksum_end("dir_check", 0.0, st);
         DIR_CHK(hipGetLastError());
         DIR_CHK(launch_excl_scan(ucount, eoff, n + 1, reinterpret_cast<int64_t *>(w + y.stmp),
@@ -559,7 +605,7 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
     if (bits & ST_TYPE_RANGE) return TG_E_TYPE_RANGE;
     if (bits) return TG_E_NOT_SIMPLE;
     if (m > 0) {
-        k_dir_edges_of<<<waves_grid(n), 256, 0, st>>>(row_ptr, col, eoff, n, esrc, eslot);
+        k_dir_edges_of<<<slots_grid(nnz), 256, 0, st>>>(row_ptr, col, eoff, n, nnz, esrc, eslot);
         int32_t *hub_id = reinterpret_cast<int32_t *>(w + y.hub_id);
         int32_t *hub_node = reinterpret_cast<int32_t *>(w + y.hub_node);
         unsigned long long *hbits = reinterpret_cast<unsigned long long *>(w + y.hbits);

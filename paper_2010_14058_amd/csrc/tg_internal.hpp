@@ -368,14 +368,15 @@ hipError_t launch_relabel(const uint32_t *sorted_ids, const uint8_t *types, cons
                           uint64_t *hub_cand, uint32_t sh_deg, const int32_t *node_graph,
                           int32_t *ngraph, const uint32_t *status, hipStream_t st);
 hipError_t launch_slot_keys(const int64_t *rp, const int32_t *col, const int64_t *ucount,
-                            const int64_t *eoff, const int32_t *newid, int64_t n, int bits,
-                            uint64_t *keys, uint32_t *vals, int32_t *ei, int32_t *ej,
+                            const int64_t *eoff, const int32_t *newid, int64_t n, int64_t nnz,
+                            int bits, uint64_t *keys, uint32_t *vals, int32_t *ei, int32_t *ej,
                             uint32_t *status, hipStream_t st);
 hipError_t launch_finish_csr(const uint64_t *keys, const uint32_t *vals, int64_t nnz, int bits,
                              const uint8_t *ntype, uint32_t *eslot, int32_t *ncol, uint32_t *neid,
                              uint8_t *ctype, const uint32_t *status, hipStream_t st);
+// nlong: the top-ranked nodes whose rows are long (a workgroup each).
 hipError_t launch_tdeg(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype, int64_t n,
-                       int L, int32_t hub_base, uint32_t *tdeg, int64_t *hstart, uint32_t *nlow,
+                       int64_t nlong, int L, int32_t hub_base, uint32_t *tdeg, int64_t *hstart, uint32_t *nlow,
                        const uint32_t *status, hipStream_t st);
 hipError_t launch_hub_build(const int64_t *nrp, const int32_t *ncol, const int64_t *hstart,
                             const uint8_t *ntype, int64_t n, int H, int Hw, int L, uint64_t *HB,
@@ -397,7 +398,7 @@ hipError_t launch_superhubs(const int64_t *nrp, const int32_t *ncol, int64_t n, 
                             uint64_t *SB, uint32_t *SP, hipStream_t st);
 hipError_t launch_node_aggr(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype,
                             const uint32_t *tri_slot, const uint32_t *tdeg,
-                            int64_t n, int L, uint64_t *A, uint64_t *D, bool ad_u32,
+                            int64_t n, int64_t nlong, int L, uint64_t *A, uint64_t *D, bool ad_u32,
                             const uint32_t *status, hipStream_t st);
 // Blocked-group candidates of the wedge-count kernel: heavy groups of at
 // least min_wedges wedges (and below 2^31) are appended to cand_a / cand_b
@@ -409,8 +410,8 @@ struct BlkSelect {
     uint64_t min_wedges_a, min_wedges_b;
 };
 hipError_t launch_cyc_work(const int64_t *nrp, const int32_t *ncol, const uint32_t *neid,
-                           const uint32_t *eslot, const uint32_t *nlow, int64_t n, uint32_t *la_l,
-                           uint4 *la_h, uint32_t *lb_l, uint4 *lb_h, uint64_t *counters,
+                           const uint32_t *eslot, const uint32_t *nlow, int64_t n, int64_t nlong,
+                           uint32_t *la_l, uint4 *la_h, uint32_t *lb_l, uint4 *lb_h, uint64_t *counters,
                            uint64_t task_wedges, int L, uint64_t range_bytes,
                            uint64_t light_max, const BlkSelect &blk, const uint32_t *status,
                            hipStream_t st);

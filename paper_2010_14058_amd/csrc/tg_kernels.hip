@@ -31,48 +31,61 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t count) {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += stride) p[q] = v;
 }
 
-// One wave per input row (grid-stride): row checks, degree, number of larger
-// neighbours.
-__global__ void k_check_rows(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-                             const uint8_t *__restrict__ types, int64_t n, int64_t nnz, int L,
-                             uint32_t *__restrict__ deg, int64_t *__restrict__ ucount,
-                             uint32_t *__restrict__ status, const int32_t *__restrict__ node_graph,
-                             const int32_t *__restrict__ gL) {
-    const int lane = lane_id();
+// One thread per input row: row bounds, type, degree, number of larger
+// neighbours (the row is searched; k_check_slots checks that it is sorted).
+__global__ void __launch_bounds__(256)
+k_check_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+              const uint8_t *__restrict__ types, int64_t n, int64_t nnz, int L,
+              uint32_t *__restrict__ deg, int64_t *__restrict__ ucount,
+              uint32_t *__restrict__ status, const int32_t *__restrict__ node_graph,
+              const int32_t *__restrict__ gL) {
     if (input_failed(status)) return;  // inconsistent batch descriptor
-    if (blockIdx.x == 0 && threadIdx.x == 0) ucount[n] = 0;  // sentinel of the exclusive scan
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE); u < n;
-         u += nwaves) {
-    int64_t b = rp[u], e = rp[u + 1];
+    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
     uint32_t bad = 0;
-    if (b < 0 || e > nnz || e < b || (u == 0 && b != 0) || (u == n - 1 && e != nnz)) {
-        if (lane == 0) {
-            atomicOr(status, ST_UNSORTED);
+    if (u < n) {
+        if (u == 0) ucount[n] = 0;  // sentinel of the exclusive scan
+        const int64_t b = rp[u], e = rp[u + 1];
+        if (b < 0 || e > nnz || e < b || (u == 0 && b != 0) || (u == n - 1 && e != nnz)) {
+            bad = ST_UNSORTED;
             deg[u] = 0;
             ucount[u] = 0;
+        } else {
+            if (types[u] >= (node_graph ? gL[node_graph[u]] : L)) bad |= ST_TYPE_RANGE;
+            deg[u] = (uint32_t)(e - b);
+            ucount[u] = e - upper_bound(col, b, e, (int32_t)u);
         }
-        continue;
     }
-    uint64_t up = 0;
-    const int32_t gu = node_graph ? node_graph[u] : 0;
-    for (int64_t s = b + lane; s < e; s += WAVE) {
-        int32_t x = col[s];
-        if (x < 0 || x >= n) bad |= ST_COL_RANGE;
-        else if (node_graph && node_graph[x] != gu) bad |= ST_CROSS_GRAPH;
-        if (x == u) bad |= ST_SELF_LOOP;
-        if (s > b && col[s - 1] >= x) bad |= ST_UNSORTED;
-        if (x > u) ++up;
-    }
-    up = wave_sum_u64(up);
     bad = wave_or(bad);
-    if (lane == 0) {
-        if (types[u] >= (node_graph ? gL[gu] : L)) bad |= ST_TYPE_RANGE;
-        deg[u] = (uint32_t)(e - b);
-        ucount[u] = (int64_t)up;
-        if (bad) atomicOr(status, bad);
+    if (lane_id() == 0 && bad) atomicOr(status, bad);
+}
+
+// The rows' entries, one per thread (rows bounds are valid here).  A wave per
+// row took 0.72 ms on the 10M-edge power law, all but 0.1 ms of it waiting for
+// the wave of its 53,000-neighbour hub.
+__global__ void __launch_bounds__(256)
+k_check_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t n,
+              int64_t nnz, uint32_t *__restrict__ status,
+              const int32_t *__restrict__ node_graph) {
+    __shared__ SlotTile T;
+    if (input_failed(status)) return;
+    uint32_t bad = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
+         s0 += (int64_t)gridDim.x * SLOT_TILE) {
+        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+        slot_tile(rp, n, s0, s1, T);
+        int64_t u = T.r0;
+        for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
+            u = slot_row(rp, T, u, s);
+            const int32_t x = col[s];
+            if (x < 0 || x >= n) bad |= ST_COL_RANGE;
+            else if (node_graph && node_graph[x] != node_graph[u]) bad |= ST_CROSS_GRAPH;
+            if (x == u) bad |= ST_SELF_LOOP;
+            if (s > slot_first(rp, T, u) && col[s - 1] >= x) bad |= ST_UNSORTED;
+        }
+        __syncthreads();
     }
-    }
+    bad = wave_or(bad);
+    if (lane_id() == 0 && bad) atomicOr(status, bad);
 }
 
 // Batch descriptor checks, one thread per graph; the largest graph's node
@@ -216,46 +229,48 @@ __global__ void k_relabel(const uint32_t *__restrict__ sorted_ids, const uint8_t
         atomicAdd((unsigned long long *)(hub_cand + 1), (unsigned long long)__popcll(sbal));
 }
 
-// One wave per input row (grid-stride): canonical edge id of every slot, the relabelled
-// slot key (row << bits | col), and the canonical endpoints of each edge.
-__global__ void k_slot_keys(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-                            const int64_t *__restrict__ ucount, const int64_t *__restrict__ eoff,
-                            const int32_t *__restrict__ newid, int64_t n, int bits,
-                            uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                            int32_t *__restrict__ ei, int32_t *__restrict__ ej,
-                            uint32_t *__restrict__ status) {
+// One thread per slot: canonical edge id of every slot, the relabelled slot
+// key (row << bits | col), and the canonical endpoints of each edge.
+__global__ void __launch_bounds__(256)
+k_slot_keys(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+            const int64_t *__restrict__ ucount, const int64_t *__restrict__ eoff,
+            const int32_t *__restrict__ newid, int64_t n, int64_t nnz, int bits,
+            uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int32_t *__restrict__ ei,
+            int32_t *__restrict__ ej, uint32_t *__restrict__ status) {
+    __shared__ SlotTile T;
     if (input_failed(status)) return;  // includes an edge count that is not nnz / 2
-    const int lane = lane_id();
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE); u < n;
-         u += nwaves) {
-    int64_t b = rp[u], e = rp[u + 1];
-    int64_t ustart = e - ucount[u];
     uint32_t bad = 0;
-    uint64_t nu = (uint64_t)newid[u];
-    for (int64_t s = b + lane; s < e; s += WAVE) {
-        int32_t x = col[s];
-        int64_t eid;
-        if (x > u) {
-            eid = eoff[u] + (s - ustart);
-            ei[eid] = (int32_t)nu;
-            ej[eid] = newid[x];
-        } else {
-            int64_t xb = rp[x], xe = rp[x + 1];
-            int64_t p = lower_bound(col, xb, xe, (int32_t)u);
-            if (p >= xe || col[p] != (int32_t)u) {
-                bad |= ST_ASYMMETRIC;
-                eid = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
+         s0 += (int64_t)gridDim.x * SLOT_TILE) {
+        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+        slot_tile(rp, n, s0, s1, T);
+        int64_t u = T.r0;
+        for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
+            u = slot_row(rp, T, u, s);
+            const int32_t x = col[s];
+            const uint64_t nu = (uint64_t)newid[u], nx = (uint64_t)newid[x];
+            int64_t eid;
+            if (x > u) {
+                eid = eoff[u + 1] - (slot_first(rp, T, u + 1) - s);
+                ei[eid] = (int32_t)nu;
+                ej[eid] = (int32_t)nx;
             } else {
-                eid = eoff[x] + (p - (xe - ucount[x]));
+                const int64_t xe = rp[x + 1], xu = xe - ucount[x];   // x's entries above x
+                const int64_t p = lower_bound(col, xu, xe, (int32_t)u);
+                if (p >= xe || col[p] != (int32_t)u) {
+                    bad |= ST_ASYMMETRIC;
+                    eid = 0;
+                } else {
+                    eid = eoff[x] + (p - xu);
+                }
             }
+            keys[s] = (nu << bits) | nx;
+            vals[s] = (uint32_t)eid;
         }
-        keys[s] = (nu << bits) | (uint64_t)newid[x];
-        vals[s] = (uint32_t)eid;
+        __syncthreads();
     }
     bad = wave_or(bad);
-    if (lane == 0 && bad) atomicOr(status, bad);
-    }
+    if (lane_id() == 0 && bad) atomicOr(status, bad);
 }
 
 // Sorted keys (row << bits | column) to the relabelled CSR, plus the slot of
@@ -280,8 +295,9 @@ __global__ void k_finish_csr(const uint64_t *__restrict__ keys, const uint32_t *
     }
 }
 
-// One wave per internal node: typed degrees d_v^t (rows padded to
-// tri_pitch(L) words) and the first slot of the row's hub suffix (neighbours with internal id >= hub_base).
+// One wave per internal node of [0, n): typed degrees d_v^t (rows
+// padded to tri_pitch(L) words), the first slot of the row's hub suffix
+// (neighbours with internal id >= hub_base) and the lower neighbours.
 __global__ void k_tdeg(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
                        const uint8_t *__restrict__ ctype, int64_t n, int L, int32_t hub_base,
                        uint32_t *__restrict__ tdeg, int64_t *__restrict__ hstart,
@@ -306,6 +322,44 @@ __global__ void k_tdeg(const int64_t *__restrict__ nrp, const int32_t *__restric
         }
         const int LP = tri_pitch(L);
         if (lane < LP) tdeg[v * LP + lane] = lane < L ? c : 0u;
+    }
+}
+
+// The same for the long rows, the top-ranked nodes first + blockIdx.x: one
+// workgroup each.  The wave of the largest row kept this kernel, the node
+// aggregates and the wedge counts waiting (0.7, 2.2 and 3.2 ms on the 10M-edge
+// power law, 53,000 neighbours; 0.56, 1.18 and 1.24 ms with a workgroup each).
+constexpr int LONG_THREADS = 1024;
+
+__global__ void __launch_bounds__(LONG_THREADS)
+k_tdeg_long(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
+            const uint8_t *__restrict__ ctype, int64_t first, int L, int32_t hub_base,
+            uint32_t *__restrict__ tdeg, int64_t *__restrict__ hstart,
+            uint32_t *__restrict__ nlow, const uint32_t *__restrict__ status) {
+    __shared__ uint32_t cnt[LONG_THREADS / WAVE][TG_MAX_L];
+    if (input_failed(status)) return;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / WAVE;
+    const int64_t v = first + blockIdx.x;
+    const int64_t b = nrp[v], e = nrp[v + 1];
+    if (tid == 0) hstart[v] = lower_bound(ncol, b, e, hub_base);
+    if (tid == WAVE) nlow[v] = (uint32_t)(lower_bound(ncol, b, e, (int32_t)v) - b);
+    uint32_t c = 0;
+    for (int64_t base = b + (int64_t)w * WAVE; base < e; base += LONG_THREADS) {
+        const int64_t s = base + lane;
+        const int t = s < e ? (int)ctype[s] : -1;
+        for (int tt = 0; tt < L; ++tt) {
+            const uint64_t bal = __ballot(t == tt);
+            if (lane == tt) c += (uint32_t)__popcll(bal);
+        }
+    }
+    if (lane < TG_MAX_L) cnt[w][lane] = c;
+    __syncthreads();
+    const int LP = tri_pitch(L);
+    if (tid < LP) {
+        uint32_t sum = 0;
+        if (tid < L)
+            for (int q = 0; q < LONG_THREADS / WAVE; ++q) sum += cnt[q][tid];
+        tdeg[v * LP + tid] = sum;
     }
 }
 
@@ -406,57 +460,95 @@ k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
 
 // One workgroup per super-hub: bitmap of its neighbours over all nodes and
 // the per-word exclusive prefix popcounts (slot of a neighbour in the row).
-__global__ void __launch_bounds__(256) k_superhubs(const int64_t *__restrict__ nrp,
-                                                   const int32_t *__restrict__ ncol, int64_t n,
-                                                   int S, int64_t nw, uint64_t *__restrict__ SB,
-                                                   uint32_t *__restrict__ SP) {
-    __shared__ uint32_t part[256];
+__global__ void __launch_bounds__(LONG_THREADS)
+k_superhubs(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol, int64_t n, int S,
+            int64_t nw, uint64_t *__restrict__ SB, uint32_t *__restrict__ SP) {
+    __shared__ uint32_t wtot[LONG_THREADS / WAVE];
     const int s = blockIdx.x;
     if (s >= S) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / WAVE;
     const int64_t v = n - S + s;
     uint64_t *bits = SB + (size_t)s * nw;
     uint32_t *pre = SP + (size_t)s * nw;
-    for (int64_t q = tid; q < nw; q += 256) bits[q] = 0ull;
+    for (int64_t q = tid; q < nw; q += LONG_THREADS) bits[q] = 0ull;
     __syncthreads();
-    for (int64_t p = nrp[v] + tid; p < nrp[v + 1]; p += 256) {
+    for (int64_t p = nrp[v] + tid; p < nrp[v + 1]; p += LONG_THREADS) {
         int32_t x = ncol[p];
         __hip_atomic_fetch_or((unsigned long long *)&bits[x >> 6], 1ull << (x & 63),
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
-    // contiguous word segments per thread, then a block scan of their sums
-    const int64_t seg = (nw + 255) / 256;
-    const int64_t q0 = tid * seg, q1 = q0 + seg < nw ? q0 + seg : nw;
-    uint32_t sum = 0;
-    for (int64_t q = q0; q < q1; ++q)
-        sum += (uint32_t)__popcll(__hip_atomic_load((unsigned long long *)&bits[q], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP));
-    part[tid] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t run = 0;
-        for (int q = 0; q < 256; ++q) {
-            uint32_t c = part[q];
-            part[q] = run;
-            run += c;
+    uint32_t run = 0;
+    for (int64_t base = 0; base < nw; base += LONG_THREADS) {
+        const int64_t q = base + tid;
+        const uint32_t c =
+            q < nw ? (uint32_t)__popcll(__hip_atomic_load((unsigned long long *)&bits[q],
+                                                          __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_WORKGROUP))
+                   : 0u;
+        const uint32_t incl = wave_incl_scan(c);
+        if (lane == WAVE - 1) wtot[w] = incl;
+        __syncthreads();
+        uint32_t before = run, all = 0;
+        for (int x = 0; x < LONG_THREADS / WAVE; ++x) {
+            if (x < w) before += wtot[x];
+            all += wtot[x];
         }
-    }
-    __syncthreads();
-    uint32_t run = part[tid];
-    for (int64_t q = q0; q < q1; ++q) {
-        pre[q] = run;
-        run += (uint32_t)__popcll(__hip_atomic_load((unsigned long long *)&bits[q], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP));
+        if (q < nw) pre[q] = before + incl - c;
+        run += all;
+        __syncthreads();
     }
 }
 
 // ------------------------------------------------------ node aggregates
 
-// One wave per internal node u; LDS holds A_u and D_u (L x L uint64 each).
-// An entry of A_u sums at most d_u triangle counts of at most d_u, one of
-// D_u at most d_u degrees, so with every degree below 2^16 both are stored
-// as uint32 (ad_u32).
+// A_u and D_u of node u (L x L uint64 each in LDS, zeroed here), by NT
+// threads.
+template <int NT>
+__device__ __forceinline__ void node_aggr(const int64_t *__restrict__ nrp,
+                                          const int32_t *__restrict__ ncol,
+                                          const uint8_t *__restrict__ ctype,
+                                          const uint32_t *__restrict__ tri_slot,
+                                          const uint32_t *__restrict__ tdeg, int64_t u, int L,
+                                          uint64_t *sA, uint64_t *sD, int tid) {
+    const int LL = L * L, LP = tri_pitch(L);
+    for (int q = tid; q < 2 * LL; q += NT) sA[q] = 0;   // sD follows sA
+    if (NT == WAVE) wave_sync(); else __syncthreads();
+    for (int64_t s = nrp[u] + tid; s < nrp[u + 1]; s += NT) {
+        const int32_t k = ncol[s];
+        const int t = ctype[s];
+        const uint32_t *ts = tri_slot + (size_t)s * LP;
+        const uint32_t *dk = tdeg + (size_t)k * LP;
+        for (int t2 = 0; t2 < L; ++t2) {
+            const uint32_t a = ts[t2];
+            const uint32_t d = dk[t2];
+            if (a) atomicAdd((unsigned long long *)&sA[t * L + t2], (unsigned long long)a);
+            if (d) atomicAdd((unsigned long long *)&sD[t * L + t2], (unsigned long long)d);
+        }
+    }
+    if (NT == WAVE) wave_sync(); else __syncthreads();
+}
+
+// Stores them: an entry of A_u sums at most d_u triangle counts of at most
+// d_u, one of D_u at most d_u degrees, so with every degree below 2^16 both
+// are stored as uint32 (ad_u32).
+__device__ __forceinline__ void store_aggr(uint64_t *A, uint64_t *D, int ad_u32, int64_t u, int LL,
+                                           const uint64_t *sA, const uint64_t *sD, int tid, int nt) {
+    if (ad_u32) {
+        uint32_t *A32 = reinterpret_cast<uint32_t *>(A), *D32 = reinterpret_cast<uint32_t *>(D);
+        for (int q = tid; q < LL; q += nt) {
+            A32[(size_t)u * LL + q] = (uint32_t)sA[q];
+            D32[(size_t)u * LL + q] = (uint32_t)sD[q];
+        }
+    } else {
+        for (int q = tid; q < LL; q += nt) {
+            A[(size_t)u * LL + q] = sA[q];
+            D[(size_t)u * LL + q] = sD[q];
+        }
+    }
+}
+
+// One wave per internal node of [0, n).
 __global__ void k_node_aggr(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
                             const uint8_t *__restrict__ ctype, const uint32_t *__restrict__ tri_slot,
                             const uint32_t *__restrict__ tdeg,
@@ -464,42 +556,29 @@ __global__ void k_node_aggr(const int64_t *__restrict__ nrp, const int32_t *__re
                             int ad_u32, const uint32_t *__restrict__ status) {
     if (input_failed(status)) return;
     extern __shared__ uint64_t sm_aggr[];
-    int w = threadIdx.x / WAVE;
-    int lane = lane_id();
-    int LL = L * L;
-    uint64_t *sA = sm_aggr + (size_t)w * 2 * LL;
-    uint64_t *sD = sA + LL;
+    const int w = threadIdx.x / WAVE, lane = lane_id(), LL = L * L;
+    uint64_t *sA = sm_aggr + (size_t)w * 2 * LL, *sD = sA + LL;
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / WAVE) + w; u < n; u += nwaves) {
-        for (int q = lane; q < LL; q += WAVE) { sA[q] = 0; sD[q] = 0; }
-        wave_sync();
-        for (int64_t s = nrp[u] + lane; s < nrp[u + 1]; s += WAVE) {
-            int32_t k = ncol[s];
-            int t = ctype[s];
-            const uint32_t *ts = tri_slot + (size_t)s * tri_pitch(L);
-            const uint32_t *dk = tdeg + (size_t)k * tri_pitch(L);
-            for (int t2 = 0; t2 < L; ++t2) {
-                uint32_t a = ts[t2];
-                uint32_t d = dk[t2];
-                if (a) atomicAdd((unsigned long long *)&sA[t * L + t2], (unsigned long long)a);
-                if (d) atomicAdd((unsigned long long *)&sD[t * L + t2], (unsigned long long)d);
-            }
-        }
-        wave_sync();
-        if (ad_u32) {
-            uint32_t *A32 = reinterpret_cast<uint32_t *>(A), *D32 = reinterpret_cast<uint32_t *>(D);
-            for (int q = lane; q < LL; q += WAVE) {
-                A32[(size_t)u * LL + q] = (uint32_t)sA[q];
-                D32[(size_t)u * LL + q] = (uint32_t)sD[q];
-            }
-        } else {
-            for (int q = lane; q < LL; q += WAVE) {
-                A[(size_t)u * LL + q] = sA[q];
-                D[(size_t)u * LL + q] = sD[q];
-            }
-        }
+        node_aggr<WAVE>(nrp, ncol, ctype, tri_slot, tdeg, u, L, sA, sD, lane);
+        store_aggr(A, D, ad_u32, u, LL, sA, sD, lane, WAVE);
         wave_sync();
     }
+}
+
+// The long rows: one workgroup each.
+__global__ void __launch_bounds__(LONG_THREADS)
+k_node_aggr_long(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
+                 const uint8_t *__restrict__ ctype, const uint32_t *__restrict__ tri_slot,
+                 const uint32_t *__restrict__ tdeg, int64_t first, int L, uint64_t *__restrict__ A,
+                 uint64_t *__restrict__ D, int ad_u32, const uint32_t *__restrict__ status) {
+    if (input_failed(status)) return;
+    extern __shared__ uint64_t sm_aggr[];
+    const int LL = L * L;
+    const int64_t u = first + blockIdx.x;
+    node_aggr<LONG_THREADS>(nrp, ncol, ctype, tri_slot, tdeg, u, L, sm_aggr, sm_aggr + LL,
+                            threadIdx.x);
+    store_aggr(A, D, ad_u32, u, LL, sm_aggr, sm_aggr + LL, threadIdx.x, LONG_THREADS);
 }
 
 // ------------------------------------------------------------ 4-cycles
@@ -1322,8 +1401,8 @@ __global__ void __launch_bounds__(1024) k_blk_setup(CycleArgs a, BlkArgs b) {
 // total checked against the wedge count of the selection; clears the
 // group's bucket counts.
 template <int PASS>
-__global__ void __launch_bounds__(256) k_blk_items(CycleArgs a, BlkArgs b) {
-    constexpr int NT = 256;
+__global__ void __launch_bounds__(1024) k_blk_items(CycleArgs a, BlkArgs b) {
+    constexpr int NT = 1024;   // a top vertex has up to 50,000 items
     __shared__ uint32_t wt[NT / WAVE];
     __shared__ uint32_t s_carry;
     if (input_failed(a.status)) return;
@@ -1760,6 +1839,21 @@ __global__ void __launch_bounds__(NT) k_blk_emit(CycleArgs a, BlkArgs b) {
 // 16-bit class; targets of smaller degree take less, of degree >= 2^16 more).
 __device__ __forceinline__ uint64_t map_bytes_per_id(int L) { return (uint64_t)((L + 1) / 2) * 4; }
 
+// Work of one pass seen by a lane: added to the counters once per wave.
+struct WorkTotals {
+    uint64_t wedges = 0, heavy_wedges = 0, heavy_groups = 0;
+};
+
+__device__ void add_totals(uint64_t *counters, int c_wedges, int c_wedges_heavy,
+                           const WorkTotals &t) {
+    const uint64_t w = wave_sum_u64(t.wedges), h = wave_sum_u64(t.heavy_wedges),
+                   g = wave_sum_u64(t.heavy_groups);
+    if (lane_id() != 0) return;
+    if (w) atomicAdd((unsigned long long *)&counters[c_wedges], (unsigned long long)w);
+    if (h) atomicAdd((unsigned long long *)&counters[c_wedges_heavy], (unsigned long long)h);
+    if (g) atomicAdd((unsigned long long *)&counters[C_HEAVY_GROUPS], (unsigned long long)g);
+}
+
 // Wave-wide list appends of the groups found by the lanes of a wave (one
 // counter update per wave and list).  Every lane of the wave calls this with
 // its own node v and wedge count w (0: no group).  Light groups go to
@@ -1767,8 +1861,8 @@ __device__ __forceinline__ uint64_t map_bytes_per_id(int L) { return (uint64_t)(
 // beyond one entry per group drawing on a shared budget of extra slots (a
 // wave whose splits do not fit keeps its groups whole).
 __device__ void push_groups(int32_t v, uint64_t w, uint32_t *light, uint4 *heavy,
-                            uint64_t *counters, int c_light, int c_heavy, int c_wedges,
-                            int c_wedges_heavy, uint64_t task_wedges, int64_t range_ids,
+                            uint64_t *counters, int c_light, int c_heavy, WorkTotals &tot,
+                            uint64_t task_wedges, int64_t range_ids,
                             uint64_t map_bytes_per_id, uint64_t range_bytes, uint64_t light_max,
                             uint2 *cand, uint64_t *chist, int c_cand, uint64_t cand_min) {
     const int lane = lane_id();
@@ -1792,14 +1886,12 @@ __device__ void push_groups(int32_t v, uint64_t w, uint32_t *light, uint4 *heavy
         base = __shfl(base, 0, WAVE);
         if (is_light) light[base + __popcll(bl & below)] = (uint32_t)v;
     }
-    uint64_t tot = wave_sum_u64(w);
-    uint64_t tot_heavy = wave_sum_u64(is_heavy ? w : 0ull);
-    if (lane == 0 && tot) atomicAdd((unsigned long long *)&counters[c_wedges], (unsigned long long)tot);
+    tot.wedges += w;
     uint64_t bh = __ballot(is_heavy);
     if (!bh) return;
-    if (lane == 0) {
-        atomicAdd((unsigned long long *)&counters[c_wedges_heavy], (unsigned long long)tot_heavy);
-        atomicAdd((unsigned long long *)&counters[C_HEAVY_GROUPS], (unsigned long long)__popcll(bh));
+    if (is_heavy) {
+        tot.heavy_wedges += w;
+        ++tot.heavy_groups;
     }
     uint32_t parts = 0;
     if (is_heavy) {
@@ -1854,25 +1946,50 @@ __device__ __forceinline__ void node_wedges(const int64_t *__restrict__ nrp,
     }
 }
 
-// Wedge counts of both passes per node, bucketed into light and heavy lists.
-// Node ids are ranked by degree, so nodes below the first one of degree >=
-// 64 are taken one per lane (64 nodes of similar degree per wave) and the
-// rest one per wave.
-__global__ void __launch_bounds__(256) k_cyc_work(
-    const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
-    const uint32_t *__restrict__ neid, const uint32_t *__restrict__ eslot,
-    const uint32_t *__restrict__ nlow, int64_t n, uint32_t *__restrict__ listA_light,
-    uint4 *__restrict__ listA_heavy, uint32_t *__restrict__ listB_light,
-    uint4 *__restrict__ listB_heavy, uint64_t *__restrict__ counters, uint64_t task_wedges,
-    int L, uint64_t range_bytes, uint64_t light_max, BlkSelect bs,
-    const uint32_t *__restrict__ status) {
-    if (input_failed(status)) return;
+struct WorkArgs {
+    const int64_t *nrp;
+    const int32_t *ncol;
+    const uint32_t *neid, *eslot, *nlow;
+    int64_t n;
+    uint32_t *listA_light;
+    uint4 *listA_heavy;
+    uint32_t *listB_light;
+    uint4 *listB_heavy;
+    uint64_t *counters;
+    uint64_t task_wedges;
+    int L;
+    uint64_t range_bytes, light_max;
+    BlkSelect bs;
+    const uint32_t *status;
+};
+
+// Lists the lane's node v (w = 0: none) in both passes.
+__device__ __forceinline__ void push_node(const WorkArgs &a, int64_t v, uint64_t wa, uint64_t wb,
+                                          WorkTotals &ta, WorkTotals &tb) {
+    push_groups((int32_t)v, wa, a.listA_light, a.listA_heavy, a.counters, C_A_LIGHT, C_A_HEAVY, ta,
+                a.task_wedges, v, map_bytes_per_id(a.L), a.range_bytes, a.light_max, a.bs.cand_a,
+                a.bs.hist_a, C_BLK_CAND_A, a.bs.min_wedges_a);
+    push_groups((int32_t)v, wb, a.listB_light, a.listB_heavy, a.counters, C_B_LIGHT, C_B_HEAVY, tb,
+                a.task_wedges, a.n - 1 - v, map_bytes_per_id(a.L), a.range_bytes, a.light_max,
+                a.bs.cand_b, a.bs.hist_b, C_BLK_CAND_B, a.bs.min_wedges_b);
+}
+
+// Wedge counts of both passes per node (the nlong long rows aside), in light
+// and heavy lists.  Node ids are ranked by degree, so nodes below the first one
+// of degree >= 64 are taken one per lane (64 nodes of similar degree per wave)
+// and the rest one after the other by a wave, up to WORK_NODES of them listed
+// together (the lists' counters are the contended words).
+constexpr int64_t WORK_NODES = 8;
+
+__global__ void __launch_bounds__(256) k_cyc_work(WorkArgs a, int64_t nlong) {
+    if (input_failed(a.status)) return;
     __shared__ int64_t s_thr;
+    const int64_t n = a.n - nlong;
     if (threadIdx.x == 0) {
         int64_t lo = 0, hi = n;
         while (lo < hi) {
             int64_t mid = (lo + hi) >> 1;
-            if (nrp[mid + 1] - nrp[mid] < WAVE) lo = mid + 1; else hi = mid;
+            if (a.nrp[mid + 1] - a.nrp[mid] < WAVE) lo = mid + 1; else hi = mid;
         }
         s_thr = lo;
     }
@@ -1882,36 +1999,61 @@ __global__ void __launch_bounds__(256) k_cyc_work(
     const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     const int64_t chunks = (thr + WAVE - 1) / WAVE;
+    WorkTotals ta, tb;
     for (int64_t c = wid; c < chunks; c += nwaves) {
         const int64_t v = c * WAVE + lane;
         uint64_t wa = 0, wb = 0;
         if (v < thr)
-            for (int64_t s = nrp[v]; s < nrp[v + 1]; ++s)
-                node_wedges(nrp, ncol, neid, eslot, nlow, (int32_t)v, s, wa, wb);
-        push_groups((int32_t)v, wa, listA_light, listA_heavy, counters, C_A_LIGHT, C_A_HEAVY,
-                    C_WEDGES_A, C_WEDGES_A_HEAVY, task_wedges, v,
-                    map_bytes_per_id(L), range_bytes, light_max, bs.cand_a, bs.hist_a, C_BLK_CAND_A,
-                    bs.min_wedges_a);
-        push_groups((int32_t)v, wb, listB_light, listB_heavy, counters, C_B_LIGHT, C_B_HEAVY,
-                    C_WEDGES_B, C_WEDGES_B_HEAVY, task_wedges, n - 1 - v,
-                    map_bytes_per_id(L), range_bytes, light_max, bs.cand_b, bs.hist_b, C_BLK_CAND_B,
-                    bs.min_wedges_b);
+            for (int64_t s = a.nrp[v]; s < a.nrp[v + 1]; ++s)
+                node_wedges(a.nrp, a.ncol, a.neid, a.eslot, a.nlow, (int32_t)v, s, wa, wb);
+        push_node(a, v, wa, wb, ta, tb);
     }
-    for (int64_t v = thr + wid; v < n; v += nwaves) {
-        uint64_t wa = 0, wb = 0;
-        for (int64_t s = nrp[v] + lane; s < nrp[v + 1]; s += WAVE)
-            node_wedges(nrp, ncol, neid, eslot, nlow, (int32_t)v, s, wa, wb);
-        wa = wave_sum_u64(wa);
-        wb = wave_sum_u64(wb);
-        push_groups((int32_t)v, lane == 0 ? wa : 0ull, listA_light, listA_heavy, counters,
-                    C_A_LIGHT, C_A_HEAVY, C_WEDGES_A, C_WEDGES_A_HEAVY, task_wedges, v,
-                    map_bytes_per_id(L), range_bytes, light_max, bs.cand_a, bs.hist_a, C_BLK_CAND_A,
-                    bs.min_wedges_a);
-        push_groups((int32_t)v, lane == 0 ? wb : 0ull, listB_light, listB_heavy, counters,
-                    C_B_LIGHT, C_B_HEAVY, C_WEDGES_B, C_WEDGES_B_HEAVY, task_wedges, n - 1 - v,
-                    map_bytes_per_id(L), range_bytes, light_max, bs.cand_b, bs.hist_b, C_BLK_CAND_B,
-                    bs.min_wedges_b);
+    int64_t per = (n - thr) / nwaves + 1;
+    if (per > WORK_NODES) per = WORK_NODES;
+    for (int64_t v0 = thr + wid * per; v0 < n; v0 += nwaves * per) {
+        uint64_t wa = 0, wb = 0;   // lane k: node v0 + k
+        for (int k = 0; k < per && v0 + k < n; ++k) {
+            const int64_t v = v0 + k;
+            uint64_t xa = 0, xb = 0;
+            for (int64_t s = a.nrp[v] + lane; s < a.nrp[v + 1]; s += WAVE)
+                node_wedges(a.nrp, a.ncol, a.neid, a.eslot, a.nlow, (int32_t)v, s, xa, xb);
+            xa = wave_sum_u64(xa);
+            xb = wave_sum_u64(xb);
+            if (lane == k) {
+                wa = xa;
+                wb = xb;
+            }
+        }
+        push_node(a, v0 + lane, wa, wb, ta, tb);
     }
+    add_totals(a.counters, C_WEDGES_A, C_WEDGES_A_HEAVY, ta);
+    add_totals(a.counters, C_WEDGES_B, C_WEDGES_B_HEAVY, tb);
+}
+
+// The long rows, one workgroup each; they are listed last, where the heavy
+// kernels start.
+__global__ void __launch_bounds__(LONG_THREADS) k_cyc_work_long(WorkArgs a, int64_t first) {
+    __shared__ uint64_t sum[2][LONG_THREADS / WAVE];
+    if (input_failed(a.status)) return;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / WAVE;
+    const int64_t v = first + blockIdx.x;
+    uint64_t wa = 0, wb = 0;
+    for (int64_t s = a.nrp[v] + tid; s < a.nrp[v + 1]; s += LONG_THREADS)
+        node_wedges(a.nrp, a.ncol, a.neid, a.eslot, a.nlow, (int32_t)v, s, wa, wb);
+    wa = wave_sum_u64(wa);
+    wb = wave_sum_u64(wb);
+    if (lane == 0) {
+        sum[0][w] = wa;
+        sum[1][w] = wb;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    wa = wave_sum_u64(lane < LONG_THREADS / WAVE ? sum[0][lane] : 0ull);
+    wb = wave_sum_u64(lane < LONG_THREADS / WAVE ? sum[1][lane] : 0ull);
+    WorkTotals ta, tb;
+    push_node(a, v, lane == 0 ? wa : 0ull, lane == 0 ? wb : 0ull, ta, tb);
+    add_totals(a.counters, C_WEDGES_A, C_WEDGES_A_HEAVY, ta);
+    add_totals(a.counters, C_WEDGES_B, C_WEDGES_B_HEAVY, tb);
 }
 
 // Global counts: divide each graphlet block by its edge count.
@@ -1988,8 +2130,12 @@ hipError_t launch_fill_u64(uint64_t *p, uint64_t v, int64_t count, hipStream_t s
 hipError_t launch_check_rows(const int64_t *rp, const int32_t *col, const uint8_t *types, int64_t n,
                              int64_t nnz, int L, uint32_t *deg, int64_t *ucount, uint32_t *status,
                              const int32_t *node_graph, const int32_t *gL, hipStream_t st) {
-    k_check_rows<<<blocks_bounded(n > 0 ? n : 1, 4, 32), 256, 0, st>>>(rp, col, types, n, nnz, L, deg, ucount, status,
-                                                       node_graph, gL);
+    k_check_nodes<<<blocks_for(n > 0 ? n : 1, 256), 256, 0, st>>>(rp, col, types, n, nnz, L, deg,
+                                                                  ucount, status, node_graph, gL);
+    LAUNCH_CHECK();
+    if (nnz == 0) return hipSuccess;
+    k_check_slots<<<blocks_bounded(nnz, SLOT_TILE, 16), 256, 0, st>>>(rp, col, n, nnz, status,
+                                                                     node_graph);
     LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2027,11 +2173,12 @@ hipError_t launch_relabel(const uint32_t *sorted_ids, const uint8_t *types, cons
 }
 
 hipError_t launch_slot_keys(const int64_t *rp, const int32_t *col, const int64_t *ucount,
-                            const int64_t *eoff, const int32_t *newid, int64_t n, int bits,
-                            uint64_t *keys, uint32_t *vals, int32_t *ei, int32_t *ej,
+                            const int64_t *eoff, const int32_t *newid, int64_t n, int64_t nnz,
+                            int bits, uint64_t *keys, uint32_t *vals, int32_t *ei, int32_t *ej,
                             uint32_t *status, hipStream_t st) {
-    k_slot_keys<<<blocks_bounded(n, 4, 32), 256, 0, st>>>(rp, col, ucount, eoff, newid, n, bits, keys, vals,
-                                                  ei, ej, status);
+    if (nnz == 0) return hipSuccess;
+    k_slot_keys<<<blocks_bounded(nnz, SLOT_TILE, 16), 256, 0, st>>>(
+        rp, col, ucount, eoff, newid, n, nnz, bits, keys, vals, ei, ej, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2047,10 +2194,16 @@ hipError_t launch_finish_csr(const uint64_t *keys, const uint32_t *vals, int64_t
 }
 
 hipError_t launch_tdeg(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype, int64_t n,
-                       int L, int32_t hub_base, uint32_t *tdeg, int64_t *hstart, uint32_t *nlow,
-                       const uint32_t *status, hipStream_t st) {
-    k_tdeg<<<blocks_bounded(n, 4, 32), 256, 0, st>>>(nrp, ncol, ctype, n, L, hub_base, tdeg,
-                                                     hstart, nlow, status);
+                       int64_t nlong, int L, int32_t hub_base, uint32_t *tdeg, int64_t *hstart,
+                       uint32_t *nlow, const uint32_t *status, hipStream_t st) {
+    if (nlong > 0) {
+        k_tdeg_long<<<(unsigned)nlong, LONG_THREADS, 0, st>>>(nrp, ncol, ctype, n - nlong, L,
+                                                              hub_base, tdeg, hstart, nlow, status);
+        LAUNCH_CHECK();
+    }
+    if (n == nlong) return hipSuccess;
+    k_tdeg<<<blocks_bounded(n - nlong, 4, 32), 256, 0, st>>>(nrp, ncol, ctype, n - nlong, L,
+                                                             hub_base, tdeg, hstart, nlow, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2071,18 +2224,24 @@ hipError_t launch_tri(const int64_t *nrp, const int32_t *ncol, const uint8_t *ct
 
 hipError_t launch_node_aggr(const int64_t *nrp, const int32_t *ncol, const uint8_t *ctype,
                             const uint32_t *tri_slot, const uint32_t *tdeg,
-                            int64_t n, int L, uint64_t *A, uint64_t *D, bool ad_u32,
-                            const uint32_t *status, hipStream_t st) {
-    size_t sh = (size_t)4 * 2 * L * L * sizeof(uint64_t);
-    k_node_aggr<<<blocks_bounded(n, 4, 32), 256, sh, st>>>(nrp, ncol, ctype, tri_slot, tdeg, n, L,
-                                                           A, D, ad_u32 ? 1 : 0, status);
+                            int64_t n, int64_t nlong, int L, uint64_t *A, uint64_t *D,
+                            bool ad_u32, const uint32_t *status, hipStream_t st) {
+    const size_t sh = (size_t)2 * L * L * sizeof(uint64_t);
+    if (nlong > 0) {
+        k_node_aggr_long<<<(unsigned)nlong, LONG_THREADS, sh, st>>>(
+            nrp, ncol, ctype, tri_slot, tdeg, n - nlong, L, A, D, ad_u32 ? 1 : 0, status);
+        LAUNCH_CHECK();
+    }
+    if (n == nlong) return hipSuccess;
+    k_node_aggr<<<blocks_bounded(n - nlong, 4, 32), 256, 4 * sh, st>>>(
+        nrp, ncol, ctype, tri_slot, tdeg, n - nlong, L, A, D, ad_u32 ? 1 : 0, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
 
 hipError_t launch_cyc_work(const int64_t *nrp, const int32_t *ncol, const uint32_t *neid,
-                           const uint32_t *eslot, const uint32_t *nlow, int64_t n, uint32_t *la_l,
-                           uint4 *la_h, uint32_t *lb_l, uint4 *lb_h, uint64_t *counters,
+                           const uint32_t *eslot, const uint32_t *nlow, int64_t n, int64_t nlong,
+                           uint32_t *la_l, uint4 *la_h, uint32_t *lb_l, uint4 *lb_h, uint64_t *counters,
                            uint64_t task_wedges, int L, uint64_t range_bytes,
                            uint64_t light_max, const BlkSelect &blk, const uint32_t *status,
                            hipStream_t st) {
@@ -2092,11 +2251,17 @@ hipError_t launch_cyc_work(const int64_t *nrp, const int32_t *ncol, const uint32
     if (err != hipSuccess) return err;
     err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (err != hipSuccess) return err;
-    int64_t want = (n + 4 * WAVE - 1) / (4 * WAVE) + 1;
+    // enough waves that those taking nodes one after the other have few each
+    int64_t want = n / WAVE + 1;
     int64_t cap = (int64_t)(cus > 0 ? cus : 256) * 16;
     unsigned grid = (unsigned)(want < cap ? want : cap);
-    k_cyc_work<<<grid, 256, 0, st>>>(nrp, ncol, neid, eslot, nlow, n, la_l, la_h, lb_l, lb_h,
-                                     counters, task_wedges, L, range_bytes, light_max, blk, status);
+    const WorkArgs a{nrp, ncol, neid, eslot, nlow, n, la_l, la_h, lb_l, lb_h, counters, task_wedges,
+                     L, range_bytes, light_max, blk, status};
+    if (n > nlong) {
+        k_cyc_work<<<grid, 256, 0, st>>>(a, nlong);
+        LAUNCH_CHECK();
+    }
+    if (nlong > 0) k_cyc_work_long<<<(unsigned)nlong, LONG_THREADS, 0, st>>>(a, n - nlong);
     LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2172,7 +2337,7 @@ static hipError_t launch_blk_pass(const CycleArgs &a, const BlkArgs &b, int64_t 
     LAUNCH_CHECK();
     k_blk_setup<PASS><<<1, 1024, 0, st>>>(a, b);
     LAUNCH_CHECK();
-    k_blk_items<PASS><<<(unsigned)b.max_groups, 256, 0, st>>>(a, b);
+    k_blk_items<PASS><<<(unsigned)b.max_groups, 1024, 0, st>>>(a, b);
     LAUNCH_CHECK();
     k_blk_hist<PASS, NT><<<wide, NT, sh_hist, st>>>(a, b);
     LAUNCH_CHECK();
@@ -2243,7 +2408,7 @@ hipError_t launch_batch_finalize(uint64_t *globals, const int32_t *gL, const int
 hipError_t launch_superhubs(const int64_t *nrp, const int32_t *ncol, int64_t n, int S, int64_t nw,
                             uint64_t *SB, uint32_t *SP, hipStream_t st) {
     if (S <= 0) return hipSuccess;
-    k_superhubs<<<(unsigned)S, 256, 0, st>>>(nrp, ncol, n, S, nw, SB, SP);
+    k_superhubs<<<(unsigned)S, LONG_THREADS, 0, st>>>(nrp, ncol, n, S, nw, SB, SP);
     LAUNCH_CHECK();
     return hipSuccess;
 }
