@@ -606,12 +606,12 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     ca.nrp = nrp; ca.ncol = ncol; ca.ntype = ntype; ca.neid = neid; ca.ctype = ctype; ca.ei = ei;
     ca.counters = counters; ca.L = L; ca.n = n; ca.NC = NC; ca.nc_u32 = words32 ? 1 : 0; ca.maps = maps;
     ca.status = status;
-    {
-        // hash slots: the smallest power of two above the light bucket
-        int lg = 1;
-        while ((int64_t(1) << lg) <= g_tune[TG_TUNE_LIGHT_WEDGES]) ++lg;
-        ca.light_log2 = lg;
-    }
+    // hash slots: the smallest power of two above the light bucket; twice the
+    // wedges of the small groups
+    const int64_t light_max = g_tune[TG_TUNE_LIGHT_WEDGES];
+    int lg_mid = 1, lg_small = 1;
+    while ((int64_t(1) << lg_mid) <= light_max) ++lg_mid;
+    while ((int64_t(1) << lg_small) < 2 * SMALL_WEDGES && lg_small < lg_mid) ++lg_small;
     ca.deg_sorted = batch ? 0 : 1;
     ca.blk_flag = nullptr;
     ca.hub_ids = 0;
@@ -627,10 +627,19 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // when the largest possible group fits it (30 us per empty launch)
     const bool any_heavy = wedge_cap > (uint64_t)g_tune[TG_TUNE_LIGHT_WEDGES];
     for (int pass = 0; pass < 2; ++pass) {
-        ca.list = pass == 0 ? la_l : lb_l;
-        ca.count_idx = pass == 0 ? C_A_LIGHT : C_B_LIGHT;
         ca.next_idx = 0;
+        ca.list = pass == 0 ? la_l : lb_l;
+        ca.list_step = 1;
+        ca.count_idx = pass == 0 ? C_A_LIGHT : C_B_LIGHT;
+        ca.light_log2 = lg_small;
         HIPCHK(launch_cycles(pass, false, ca, light_grid, st));
+        if (light_max > SMALL_WEDGES) {
+            ca.list += n - 1;
+            ca.list_step = -1;
+            ca.count_idx = pass == 0 ? C_A_MID : C_B_MID;
+            ca.light_log2 = lg_mid;
+            HIPCHK(launch_cycles(pass, false, ca, light_grid, st));
+        }
         timing_mark(pass == 0 ? "cycA_light" : "cycB_light");
         if (blk_pass[pass]) {
             BlkArgs bk;
@@ -785,7 +794,8 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     HIPCHK(hipMemcpyAsync(cnt_host, counters, sizeof(cnt_host), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     g_timing.stats[0] = (int64_t)cnt_host[C_WEDGES_A];
-    g_timing.stats[1] = (int64_t)(cnt_host[C_A_LIGHT] + cnt_host[C_B_LIGHT]);
+    g_timing.stats[1] = (int64_t)(cnt_host[C_A_LIGHT] + cnt_host[C_B_LIGHT] + cnt_host[C_A_MID] +
+                                  cnt_host[C_B_MID]);
     g_timing.stats[2] = (int64_t)cnt_host[C_HEAVY_GROUPS];
     g_timing.stats[3] = (int64_t)cnt_host[C_EDGE_HEAVY];
     g_timing.stats[4] = (int64_t)cnt_host[C_WEDGES_B];

@@ -31,6 +31,7 @@ constexpr uint32_t ST_INPUT = ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_TYP
                               ST_ASYMMETRIC | ST_BATCH | ST_CROSS_GRAPH | ST_EDGE_COUNT;
 
 // Tunables of the cycle and clique passes.
+constexpr int64_t SMALL_WEDGES = 128; // light groups of the small table
 constexpr int64_t LIGHT_MAXW = 512;   // a group is light if it has at most this many wedges
 // Threads of a heavy 4-cycle workgroup, per pass: pass A's maps are spread
 // over all ids, so fewer, larger workgroups (fewer maps sharing an XCD's L2)
@@ -136,7 +137,7 @@ enum Counter {
     C_BLK_NEXT_E,                           // eight emit queues, one per XCD
     C_BLK_NEXT_E_END = C_BLK_NEXT_E + 8,
     C_DIRECT_STEPS = C_BLK_NEXT_E_END, C_DIRECT_DEG, C_DIRECT_ON,
-    C_EDGE_FEW, C_EDGE_LIGHT,
+    C_EDGE_FEW, C_EDGE_LIGHT, C_A_MID, C_B_MID,
     C_NUM
 };
 
@@ -181,7 +182,8 @@ struct CycleArgs {
     const uint32_t *neid;
     const uint8_t *ctype;      // type of the neighbour at each adjacency slot
     const int32_t *ei;
-    const uint32_t *list;      // light groups
+    const uint32_t *list;      // light groups: entry q at list[q * list_step]
+    int list_step;             // 1 (small groups, from the front) or -1 (from the back)
     const uint4 *tasks;        // heavy tasks: group, part, parts, wedges of the group
     const uint32_t *eslot;     // [2e] slot of edge e in the row of its smaller end, [2e+1] larger end
     const uint32_t *nlow;      // neighbours below the node itself, per node
