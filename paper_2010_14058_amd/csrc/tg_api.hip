@@ -570,7 +570,20 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     timing_mark("aggr");
 
     // ---- 4-cycles from degree-ordered wedges
-    HIPCHK(launch_fill_u64(NC, 0, words32 ? (m * LL + 1) / 2 : m * LL, st));
+    // no per-edge table: only the sums behind the global counts, in copies in
+    // the space of the per-edge 4-cycle counts, with the rank table behind them
+    const int64_t gwords = L <= GLOBALS_MAX_L ? globals_words(L) : 1;
+    int64_t copies = (m * LL - 512) / gwords;   // the table takes at most 324 words
+    if (copies > GLOBALS_COPIES) copies = GLOBALS_COPIES;
+    const bool globals = !batch && !pa && !per_edge && global_counts && L <= GLOBALS_MAX_L &&
+                         words32 && copies > 0;
+    uint16_t *r4 = globals ? reinterpret_cast<uint16_t *>(NC + copies * gwords) : nullptr;
+    if (globals) {
+        HIPCHK(launch_fill_u64(NC, 0, copies * gwords, st));
+        HIPCHK(launch_rank4_table(L, r4, st));
+    } else {
+        HIPCHK(launch_fill_u64(NC, 0, words32 ? (m * LL + 1) / 2 : m * LL, st));
+    }
     // blocked path: counts of a blocked group's targets never exceed their
     // degree, held in 16-bit fields
     const bool blk_on = y.blk_groups > 0 && !batch && words32 && L <= 16;
@@ -613,6 +626,10 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     while ((int64_t(1) << lg_mid) <= light_max) ++lg_mid;
     while ((int64_t(1) << lg_small) < 2 * SMALL_WEDGES && lg_small < lg_mid) ++lg_small;
     ca.deg_sorted = batch ? 0 : 1;
+    ca.c4 = globals ? NC + globals_c4(L) : nullptr;
+    ca.c4_copies = (int)copies;
+    ca.c4_stride = gwords;
+    ca.r4 = r4;
     ca.blk_flag = nullptr;
     ca.hub_ids = 0;
     ca.max_deg = max_deg;
@@ -621,12 +638,13 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     // most one group per node: a grid of 262,144 workgroups that find no
     // group costs 0.23 ms per pass (a graph of 20 nodes), 6 us sized by n
     int64_t light_wgs = (int64_t)cus * 1024;
+    if (globals) light_wgs = (int64_t)cus * 32;   // each ends by adding its sums
     if (light_wgs > n) light_wgs = n;
     const unsigned light_grid = (unsigned)light_wgs;
     // a heavy group has more wedges than the light bucket: none can exist
     // when the largest possible group fits it (30 us per empty launch)
     const bool any_heavy = wedge_cap > (uint64_t)g_tune[TG_TUNE_LIGHT_WEDGES];
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < (globals ? 1 : 2); ++pass) {
         ca.next_idx = 0;
         ca.list = pass == 0 ? la_l : lb_l;
         ca.list_step = 1;
@@ -727,6 +745,8 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     ea.goff = batch ? batch->goff : nullptr;
     ea.G = batch ? batch->G : 1;
     if (batch) ea.gacc = global_counts;
+    ea.few_list = val_b;
+    ea.light_list = le + (m > 0 ? m - 1 : 0);
     uint64_t *xyk = y.defer ? at<uint64_t>(ws, y.off_xyk) : nullptr;
     ea.xyk = xyk;
     ea.xyk_u32 = words32 ? 1 : 0;
@@ -735,54 +755,57 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         ea.hist_in_lds = 0;
         ea.derive_batch = 1;
     }
-    // edge costs are very uneven: many small workgroups balance the light
-    // kernel far better than a few long grid-stride loops, except where each
-    // workgroup ends by flushing a whole global histogram (fused, one graph)
-    const int64_t per_cu = (xyk || batch) ? 2048 : 24;
-    unsigned edge_grid = (unsigned)(cus * per_cu);
-    // the eight-lane kernel's sums are 32-bit and kept for the separate
-    // derivation
-    ea.few_max = xyk && words32 ? FEW_MAX : 0;
-    ea.few_list = val_b;
-    ea.light_list = le + (m > 0 ? m - 1 : 0);
-    int64_t units = batch ? (m + BATCH_EDGE_CHUNK - 1) / BATCH_EDGE_CHUNK : m;
-    if ((int64_t)edge_grid > units) edge_grid = (unsigned)(units > 0 ? units : 1);
-    if (xyk && m > 0) HIPCHK(launch_edge_classes(ea, cus, st));
-    if (ea.few_max > 0 && m > 0) HIPCHK(launch_edges_few(ea, edge_grid, st));
-    HIPCHK(launch_edges(false, ea, edge_grid, st));
-    timing_mark("edges_light");
-    EdgeArgs eh = ea;
-    if (batch) eh.hist_in_lds = 0;  // heavy edges of many graphs: direct per-graph atomics
-    else eh.hist_in_lds = ea.hist_in_lds ? 1 : 0;
-    eh.derive_batch = 1;
-    if (xyk) eh.hist_in_lds = 0;
-    // a heavy edge's smaller end exceeds the cut: none can exist when the
-    // largest degree does not (50 us for an empty launch)
-    if (max_deg > ecut) HIPCHK(launch_edges(true, eh, (unsigned)y.heavy_edge_slots, st));
-    timing_mark("edges_heavy");
-    if (pa) {
-        const PaLayout pl = pa_layout(L);
-        uint64_t *pacc = at<uint64_t>(ws, y.off_pacc);
-        HIPCHK(launch_fill_u64(pacc, 0, pl.gstart[9], st));
-        ed.gacc = pacc;
-        ed.gw = (int)pl.gstart[9];
-        ed.hist_in_lds = (size_t)ed.gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
-        HIPCHK(launch_derive_pa(ed, pl, (unsigned)(cus * 8), st));
-        timing_mark("derive");
-        if (global_counts) HIPCHK(launch_pa_finalize(pacc, pl, global_counts, status, st));
+    if (globals) {
+        HIPCHK(launch_globals(ea, eslot, r4, NC, (int)copies, cus, global_counts, st));
         timing_mark("global");
-    } else if (xyk) {
-        ed.hist_in_lds = (size_t)gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
-        HIPCHK(launch_derive(ed, (unsigned)(cus * 8), st));
-        timing_mark("derive");
+    } else {
+        // edge costs are very uneven: many small workgroups balance the light
+        // kernel far better than a few long grid-stride loops, except where each
+        // workgroup ends by flushing a whole global histogram (fused, one graph)
+        const int64_t per_cu = (xyk || batch) ? 2048 : 24;
+        unsigned edge_grid = (unsigned)(cus * per_cu);
+        // the eight-lane kernel's sums are 32-bit and kept for the separate
+        // derivation
+        ea.few_max = xyk && words32 ? FEW_MAX : 0;
+        int64_t units = batch ? (m + BATCH_EDGE_CHUNK - 1) / BATCH_EDGE_CHUNK : m;
+        if ((int64_t)edge_grid > units) edge_grid = (unsigned)(units > 0 ? units : 1);
+        if (xyk && m > 0) HIPCHK(launch_edge_classes(ea, cus, st));
+        if (ea.few_max > 0 && m > 0) HIPCHK(launch_edges_few(ea, edge_grid, st));
+        HIPCHK(launch_edges(false, ea, edge_grid, st));
+        timing_mark("edges_light");
+        EdgeArgs eh = ea;
+        if (batch) eh.hist_in_lds = 0;  // heavy edges of many graphs: direct per-graph atomics
+        else eh.hist_in_lds = ea.hist_in_lds ? 1 : 0;
+        eh.derive_batch = 1;
+        if (xyk) eh.hist_in_lds = 0;
+        // a heavy edge's smaller end exceeds the cut: none can exist when the
+        // largest degree does not (50 us for an empty launch)
+        if (max_deg > ecut) HIPCHK(launch_edges(true, eh, (unsigned)y.heavy_edge_slots, st));
+        timing_mark("edges_heavy");
+        if (pa) {
+            const PaLayout pl = pa_layout(L);
+            uint64_t *pacc = at<uint64_t>(ws, y.off_pacc);
+            HIPCHK(launch_fill_u64(pacc, 0, pl.gstart[9], st));
+            ed.gacc = pacc;
+            ed.gw = (int)pl.gstart[9];
+            ed.hist_in_lds = (size_t)ed.gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
+            HIPCHK(launch_derive_pa(ed, pl, (unsigned)(cus * 8), st));
+            timing_mark("derive");
+            if (global_counts) HIPCHK(launch_pa_finalize(pacc, pl, global_counts, status, st));
+            timing_mark("global");
+        } else if (xyk) {
+            ed.hist_in_lds = (size_t)gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
+            HIPCHK(launch_derive(ed, (unsigned)(cus * 8), st));
+            timing_mark("derive");
+        }
+        if (pa) {
+            // position-aware globals done above
+        } else if (batch)
+            HIPCHK(launch_batch_finalize(global_counts, batch->gL, batch->goff, batch->G, status, st));
+        else if (global_counts)
+            HIPCHK(launch_global_finalize(gacc, L, gw, global_counts, status, st));
+        if (!pa) timing_mark("global");
     }
-    if (pa) {
-        // position-aware globals done above
-    } else if (batch)
-        HIPCHK(launch_batch_finalize(global_counts, batch->gL, batch->goff, batch->G, status, st));
-    else if (global_counts)
-        HIPCHK(launch_global_finalize(gacc, L, gw, global_counts, status, st));
-    if (!pa) timing_mark("global");
 
     if (async) {
         HIPCHK(launch_status_code(status, status_out, st));

@@ -899,7 +899,8 @@ __device__ __forceinline__ int edge_class(const EdgeArgs &a, int64_t e) {
     return (int64_t)t <= a.few_max && d <= FEW_DEG ? EDGE_FEW : EDGE_LIGHT;
 }
 
-// Lists of the edges of each class (separate derivation): few and heavy edges
+// Lists of the edges of each class (separate derivation; CLIQUES: of two or
+// more triangles, for the global counts): few and heavy edges
 // from the front of their lists, light ones from the back of the heavy list.
 // One atomic per class and workgroup.  The lists keep a hub's edges, which are
 // consecutive, on different waves: a wave that took 64 consecutive edges itself
@@ -907,6 +908,7 @@ __device__ __forceinline__ int edge_class(const EdgeArgs &a, int64_t e) {
 // light edges went from 2.9 to 5.8 ms).
 constexpr int CLASS_THREADS = 1024;
 
+template <bool CLIQUES>
 __global__ void __launch_bounds__(CLASS_THREADS) k_edge_classes(EdgeArgs a) {
     __shared__ uint32_t cnt[3][CLASS_THREADS / WAVE];
     __shared__ unsigned long long base[3];
@@ -915,7 +917,9 @@ __global__ void __launch_bounds__(CLASS_THREADS) k_edge_classes(EdgeArgs a) {
     for (int64_t e0 = (int64_t)blockIdx.x * CLASS_THREADS; e0 < a.m;
          e0 += (int64_t)gridDim.x * CLASS_THREADS) {
         const int64_t e = e0 + threadIdx.x;
-        const int c = e < a.m ? edge_class(a, e) : EDGE_NONE;
+        const int c = e >= a.m ? EDGE_NONE
+                      : !CLIQUES ? edge_class(a, e)
+                      : a.ttot[e] >= 2 ? EDGE_FEW : EDGE_NONE;
         uint64_t bal[3];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -1399,10 +1403,12 @@ hipError_t launch_edges(bool heavy, const EdgeArgs &args, unsigned grid, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st) {
+hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st, bool cliques) {
+    if (args.m == 0) return hipSuccess;
     int64_t grid = (args.m + CLASS_THREADS - 1) / CLASS_THREADS;
     if (grid > 8 * (int64_t)cus) grid = 8 * (int64_t)cus;
-    k_edge_classes<<<(unsigned)grid, CLASS_THREADS, 0, st>>>(args);
+    if (cliques) k_edge_classes<true><<<(unsigned)grid, CLASS_THREADS, 0, st>>>(args);
+    else k_edge_classes<false><<<(unsigned)grid, CLASS_THREADS, 0, st>>>(args);
     return hipGetLastError();
 }
 

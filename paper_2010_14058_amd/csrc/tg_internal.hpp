@@ -80,6 +80,11 @@ constexpr int64_t DIRECT_EDGES = 1 << 16;
 constexpr int DIRECT_DEG = 512;
 constexpr uint64_t DIRECT_STEPS = uint64_t(1) << 27;
 
+// Global counts of a single graph without its per-edge table (tg_globals.hip):
+// up to this many types (type masks in registers), copies of the sums.
+constexpr int GLOBALS_MAX_L = 8;
+constexpr int GLOBALS_COPIES = 64;
+
 // Batches of graphs of at most this many nodes are counted graph by graph in
 // LDS when only global counts are asked for (tg_small.hip): 512 rows of 512
 // bits take 37 KB.
@@ -201,6 +206,12 @@ struct CycleArgs {
     int light_log2;            // log2 of the light kernel's hash slots (> light bucket)
     int deg_sorted;            // node ids ranked by degree (not the graph-major batch order)
     int64_t max_deg;           // largest degree (or a bound)
+    // global counts only: the 4-cycle sums per type multiset (copies of stride
+    // words) and the rank table; null: per-edge counts
+    uint64_t *c4;
+    int c4_copies;
+    int64_t c4_stride;
+    const uint16_t *r4;
     const uint8_t *blk_flag;   // groups counted by the blocked path (skipped by the tasks), or null
     int hub_ids;               // task kernel: targets among the top hub_ids ids counted in LDS (0: none)
 };
@@ -306,6 +317,13 @@ hipError_t launch_small_batch(const int64_t *rp, const int32_t *col, const uint8
                               int64_t n, int64_t nnz, const BatchIn &b, int max_nodes, int L_max,
                               int cus, const uint32_t *list, uint64_t *counters, uint64_t *out,
                               uint32_t *status, hipStream_t st);
+
+// Global counts of a single graph (tg_globals.hip).
+int globals_words(int L);
+int globals_c4(int L);
+hipError_t launch_rank4_table(int L, uint16_t *r4, hipStream_t st);
+hipError_t launch_globals(const EdgeArgs &a, const uint32_t *eslot, const uint16_t *r4,
+                          uint64_t *acc, int copies, int cus, uint64_t *out, hipStream_t st);
 
 // Position-aware rows (tg_position.hip): blocks in row order; a block is L
 // wide (3-node), L^2 (ordered role pairs) or L(L+1)/2 (unordered pairs).
@@ -426,7 +444,8 @@ int heavy_chunk_for(int L, int threads, int hub_ids = 0, bool t32 = false);
 int heavy_hub_ids(int L, int64_t n, int64_t bytes);
 hipError_t launch_cycles(int pass, bool heavy, const CycleArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_edges(bool heavy, const EdgeArgs &args, unsigned grid, hipStream_t st);
-hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st);
+// cliques: list only the edges of two or more triangles, all as few edges.
+hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st, bool cliques = false);
 hipError_t launch_edges_few(const EdgeArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_derive(const EdgeArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_global_finalize(const uint64_t *gacc, int L, int gw, uint64_t *out,

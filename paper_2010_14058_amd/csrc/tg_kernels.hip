@@ -653,6 +653,45 @@ __device__ __forceinline__ void nc_add(const CycleArgs &a, size_t idx, uint64_t 
         atomicAdd((unsigned long long *)&a.NC[idx], (unsigned long long)v);
 }
 
+// Global counts only: 4-cycle sums per type multiset in LDS, added to a copy of
+// the call's sums at the end.  The top node's and the target's types pick a row
+// of the rank table, a centre pair's types its entry; a wedge whose target has
+// c other centres of type t adds c at its own type and t, so that every cycle
+// is met from both centres.
+struct C4Sums {
+    unsigned long long *sum;
+    uint16_t *r4;
+    int P, n4;
+};
+
+__device__ __forceinline__ int c4_pair(int a, int b) {
+    return a <= b ? a + b * (b + 1) / 2 : b + a * (a + 1) / 2;
+}
+
+// lds: 8-byte aligned, c4_lds(L) bytes; the caller synchronises after it.
+__device__ __forceinline__ C4Sums c4_begin(const CycleArgs &a, void *lds) {
+    C4Sums c;
+    c.P = a.L * (a.L + 1) / 2;
+    c.n4 = c.P * (a.L + 2) / 3 * (a.L + 3) / 4;
+    c.sum = static_cast<unsigned long long *>(lds);
+    c.r4 = reinterpret_cast<uint16_t *>(c.sum + c.n4);
+    for (int q = threadIdx.x; q < c.n4; q += blockDim.x) c.sum[q] = 0ull;
+    for (int q = threadIdx.x; q < c.P * c.P; q += blockDim.x) c.r4[q] = a.r4[q];
+    return c;
+}
+
+// After a synchronisation.
+__device__ __forceinline__ void c4_end(const CycleArgs &a, const C4Sums &c) {
+    uint64_t *out = a.c4 + (int64_t)(blockIdx.x % (unsigned)a.c4_copies) * a.c4_stride;
+    for (int q = threadIdx.x; q < c.n4; q += blockDim.x)
+        if (c.sum[q]) atomicAdd((unsigned long long *)&out[q], c.sum[q]);
+}
+
+static size_t c4_lds(int L) {
+    const size_t P = (size_t)L * (L + 1) / 2, n4 = P * (L + 2) / 3 * (L + 3) / 4;
+    return n4 * sizeof(uint64_t) + P * P * sizeof(uint16_t) + 8;
+}
+
 // Light groups: one 64-thread workgroup per group, LDS open-addressing map
 // keyed by target with 16-bit counters per type.  Two launches by size: groups
 // of at most SMALL_WEDGES wedges (from the front of the list) with 256 slots,
@@ -665,7 +704,7 @@ __device__ __forceinline__ void nc_add(const CycleArgs &a, size_t idx, uint64_t 
 // groups in flight: with one 1024-slot table per workgroup, cleared whole, and
 // two staged walks, the light groups of a 1M-edge request took 1.5 ms and those
 // of the 10M-edge power law 4.8 ms; now 0.70 and 2.5 ms.
-template <int PASS, int K>
+template <int PASS, int K, bool GLOB>
 __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
     extern __shared__ uint32_t sm_light[];
     const int L = a.L, LL = L * L;
@@ -685,6 +724,8 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
     if (blockIdx.x >= count) return;
     for (int q = lane; q < HC; q += WAVE) keys[q] = EMPTY_KEY;
     for (int q = lane; q < HC * LW; q += WAVE) cnt[q] = 0;
+    C4Sums C;
+    if constexpr (GLOB) C = c4_begin(a, cnt + (((size_t)HC * (LW + 1) + 1) & ~(size_t)1) - HC);
     wave_sync();
     // stages the items cb + lane of group g; returns their wedges
     auto stage = [&](int32_t g, int64_t cb, int64_t ie) {
@@ -718,8 +759,18 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
         atomicOr(a.status, ST_INTERNAL);
         return -1;
     };
-    auto emit = [&](int o, int h, int ty) {
-        const int tx = it_tx[o], flip = it_flip[o];
+    auto emit = [&](int o, int h, int ty, int tv) {
+        const int tx = it_tx[o];
+        if constexpr (GLOB) {
+            const uint16_t *rt = C.r4 + c4_pair(tv, ty) * C.P;
+            for (int t = 0; t < L; ++t) {
+                const uint32_t c = (cnt[h * LW + (t >> 1)] >> ((t & 1) * 16)) & 0xffffu;
+                const uint32_t val = c - (t == tx ? 1u : 0u);
+                if (val) atomicAdd(&C.sum[rt[c4_pair(tx, t)]], (unsigned long long)val);
+            }
+            return;
+        }
+        const int flip = it_flip[o];
         const size_t nc0 = (size_t)it_eid[o] * LL;
         for (int t = 0; t < L; ++t) {
             const uint32_t c = (cnt[h * LW + (t >> 1)] >> ((t & 1) * 16)) & 0xffffu;
@@ -732,6 +783,7 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
     };
     for (uint64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
         const int32_t g = (int32_t)a.list[a.list_step * (int64_t)idx];
+        const int tv = GLOB ? (int)a.ntype[g] : 0;
         int64_t ib, ie;
         item_range<PASS>(a, g, ib, ie);
         if (ie - ib <= WAVE) {
@@ -768,7 +820,7 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
             wave_sync();
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                if (hs[k] >= 0) emit(ow[k], hs[k], ty[k]);
+                if (hs[k] >= 0) emit(ow[k], hs[k], ty[k], tv);
             wave_sync();
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -790,7 +842,7 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
                     const int h = claim((uint32_t)a.ncol[ys]);   // found again in phase 1
                     if (h < 0) continue;
                     if (phase == 0) atomicAdd(&cnt[h * LW + (it_tx[o] >> 1)], 1u << ((it_tx[o] & 1) * 16));
-                    else emit(o, h, a.ctype[ys]);
+                    else emit(o, h, a.ctype[ys], tv);
                 }
                 wave_sync();
             }
@@ -799,6 +851,7 @@ __global__ void __launch_bounds__(64) k_cyc_light(CycleArgs a) {
         for (int q = lane; q < HC * LW; q += WAVE) cnt[q] = 0;
         wave_sync();
     }
+    if constexpr (GLOB) c4_end(a, C);
 }
 
 // Block-wide inclusive scan of up to NT/2 values held by threads [0, NT/2);
@@ -923,7 +976,7 @@ __device__ MapClasses map_classes(const CycleArgs &a) {
 // target sized by the target's degree class (above).  The entries of the
 // range are cleared by streaming zeros over its word range when that is
 // cheaper than a walk over the wedges; then a count walk and an emit walk.
-template <int PASS, int NT>
+template <int PASS, int NT, bool GLOB>
 __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
     constexpr int HEAVY_THREADS = NT;
     constexpr int HEAVY_CHUNK = NT / 2;
@@ -957,6 +1010,8 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
     uint64_t count = a.counters[a.count_idx];
     if (blockIdx.x >= count) return;  // more workgroups than tasks
     if (tid == 0) s_mc = map_classes(a);
+    C4Sums C;   // in the tallies' space, which the global counts do not use
+    if constexpr (GLOB) C = c4_begin(a, sm_heavy);
     __syncthreads();
     while (true) {
         if (tid == 0) {
@@ -1044,7 +1099,7 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
                 }
                 block_scan_chunk<NT>(len, it_scan, wave_tot);
                 uint32_t total = it_scan[nitems - 1];
-                if (phase == 2) {
+                if (!GLOB && phase == 2) {
                     const int words = t32 ? nitems * LL * TALLY_COPIES / 2 : nitems * LL;
                     for (int q = tid; q < words; q += HEAVY_THREADS) acc[q] = 0;
                     __syncthreads();
@@ -1102,6 +1157,7 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
                         const uint32_t mask = bits == 32 ? 0xffffffffu : (1u << bits) - 1u;
                         int wq = -1;
                         uint32_t word = 0;
+                        const uint16_t *rt = GLOB ? C.r4 + c4_pair(a.ntype[g], ty) * C.P : nullptr;
                         for (int t = 0; t < L; ++t) {
                             if (t / F != wq) {
                                 wq = t / F;
@@ -1111,7 +1167,9 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
                             const uint32_t c = (word >> ((t % F) * bits)) & mask;
                             const uint32_t val = c - (t == tx ? 1u : 0u);
                             if (!val) continue;
-                            if (t32)
+                            if constexpr (GLOB)
+                                atomicAdd(&C.sum[rt[c4_pair(tx, t)]], (unsigned long long)val);
+                            else if (t32)
                                 atomicAdd(&ac32[pass_entry<PASS>(t, ty, L) * TALLY_COPIES], val);
                             else
                                 atomicAdd((unsigned long long *)&ac[pass_entry<PASS>(t, ty, L)],
@@ -1120,7 +1178,7 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
                     }
                 }
                 __syncthreads();
-                if (phase == 2) {
+                if (!GLOB && phase == 2) {
                     for (int q = tid; q < nitems * LL; q += HEAVY_THREADS) {
                         uint64_t v = 0;
                         if (t32) {
@@ -1144,6 +1202,7 @@ __global__ void __launch_bounds__(NT) k_cyc_heavy(CycleArgs a) {
             __syncthreads();
         }
     }
+    if constexpr (GLOB) c4_end(a, C);
 }
 
 // ------------------------------------------------ blocked heavy 4-cycle groups
@@ -1649,7 +1708,7 @@ __global__ void __launch_bounds__(NT) k_blk_part(CycleArgs a, BlkArgs b) {
 // target's entry to the group's map in the degree-class layout and clear
 // its fields, so the counts are zero again for the next bucket.  Only
 // reached targets are written, and only reached targets are read.
-template <int PASS>
+template <int PASS, bool GLOB>
 __global__ void __launch_bounds__(BLK_COUNT_THREADS) k_blk_count(CycleArgs a, BlkArgs b) {
     constexpr int NT = BLK_COUNT_THREADS;
     extern __shared__ uint32_t sm_cnt[];  // BLK_IDS * L 16-bit fields, then BLK_IDS claim bits
@@ -1666,6 +1725,8 @@ __global__ void __launch_bounds__(BLK_COUNT_THREADS) k_blk_count(CycleArgs a, Bl
     uint32_t *claim = sm_cnt + words;
     for (int q = tid; q < words + BLK_IDS / 32; q += NT) sm_cnt[q] = 0u;
     if (tid == 0) s_mc = map_classes(a);
+    C4Sums C;
+    if constexpr (GLOB) C = c4_begin(a, sm_cnt + ((words + BLK_IDS / 32 + 1) & ~1));
     __syncthreads();
     const MapClasses mc = s_mc;
     // thread 0 takes the next bucket while the workgroup counts the current
@@ -1748,6 +1809,31 @@ __global__ void __launch_bounds__(BLK_COUNT_THREADS) k_blk_count(CycleArgs a, Bl
             if (atomicOr(&claim[off & (BLK_IDS / 32 - 1)], bit) & bit) continue;
             const int32_t wid = (int32_t)(id0 + off);
             const uint32_t base = off * (uint32_t)L;
+            if constexpr (GLOB) {
+                // the target's centre pairs, twice each
+                const uint16_t *rt = C.r4 + c4_pair(a.ntype[g], a.ntype[wid]) * C.P;
+                uint32_t c[GLOBALS_MAX_L];
+#pragma unroll
+                for (int t = 0; t < GLOBALS_MAX_L; ++t) {
+                    c[t] = 0u;
+                    if (t >= L) continue;
+                    const uint32_t idx = base + t;
+                    const uint32_t sh = (idx & 1u) * 16u;
+                    c[t] = (sm_cnt[idx >> 1] >> sh) & 0xffffu;
+                    if (c[t]) atomicAnd(&sm_cnt[idx >> 1], ~(0xffffu << sh));
+                }
+#pragma unroll
+                for (int u = 0; u < GLOBALS_MAX_L; ++u) {
+                    if (!c[u]) continue;
+#pragma unroll
+                    for (int t = 0; t < u; ++t)
+                        if (c[t]) atomicAdd(&C.sum[rt[t + u * (u + 1) / 2]],
+                                            2ull * c[t] * c[u]);
+                    if (c[u] > 1) atomicAdd(&C.sum[rt[u + u * (u + 1) / 2]],
+                                            (unsigned long long)c[u] * (c[u] - 1));
+                }
+                continue;
+            }
             const int cls = map_class(mc, wid);
             const int bits = class_bits(cls);
             const int F = 32 / bits;
@@ -1770,6 +1856,7 @@ __global__ void __launch_bounds__(BLK_COUNT_THREADS) k_blk_count(CycleArgs a, Bl
         for (int q = tid; q < BLK_IDS / 32; q += NT) claim[q] = 0u;
         __syncthreads();
     }
+    if constexpr (GLOB) c4_end(a, C);
 }
 
 // Emit walk: one walk task at a time; each wedge reads its target's entry
@@ -2352,16 +2439,25 @@ hipError_t launch_cycles(int pass, bool heavy, const CycleArgs &args, unsigned g
         const size_t sh = ((size_t)1 << args.light_log2) * (1 + (args.L + 1) / 2) * sizeof(uint32_t);
         constexpr int KS = (int)(SMALL_WEDGES / WAVE), KL = (int)(LIGHT_MAXW / WAVE);
         const bool small = args.list_step > 0;
-        if (pass == 0 && small) k_cyc_light<0, KS><<<grid, 64, sh, st>>>(args);
-        else if (pass == 0) k_cyc_light<0, KL><<<grid, 64, sh, st>>>(args);
-        else if (small) k_cyc_light<1, KS><<<grid, 64, sh, st>>>(args);
-        else k_cyc_light<1, KL><<<grid, 64, sh, st>>>(args);
+        if (args.c4) {
+            const size_t sg = sh + c4_lds(args.L);
+            if (small) k_cyc_light<0, KS, true><<<grid, 64, sg, st>>>(args);
+            else k_cyc_light<0, KL, true><<<grid, 64, sg, st>>>(args);
+        } else if (pass == 0) {
+            if (small) k_cyc_light<0, KS, false><<<grid, 64, sh, st>>>(args);
+            else k_cyc_light<0, KL, false><<<grid, 64, sh, st>>>(args);
+        } else {
+            if (small) k_cyc_light<1, KS, false><<<grid, 64, sh, st>>>(args);
+            else k_cyc_light<1, KL, false><<<grid, 64, sh, st>>>(args);
+        }
+    } else if (args.c4) {
+        k_cyc_heavy<0, HEAVY_THREADS_A, true><<<grid, HEAVY_THREADS_A, c4_lds(args.L), st>>>(args);
     } else {
         size_t sh = (size_t)args.chunk * args.L * args.L *
                         (args.nc_u32 ? sizeof(uint32_t) * TALLY_COPIES : sizeof(uint64_t)) +
                     (size_t)((args.hub_ids * args.L + 1) / 2) * sizeof(uint32_t);
-        if (pass == 0) k_cyc_heavy<0, HEAVY_THREADS_A><<<grid, HEAVY_THREADS_A, sh, st>>>(args);
-        else k_cyc_heavy<1, HEAVY_THREADS_B><<<grid, HEAVY_THREADS_B, sh, st>>>(args);
+        if (pass == 0) k_cyc_heavy<0, HEAVY_THREADS_A, false><<<grid, HEAVY_THREADS_A, sh, st>>>(args);
+        else k_cyc_heavy<1, HEAVY_THREADS_B, false><<<grid, HEAVY_THREADS_B, sh, st>>>(args);
     }
     LAUNCH_CHECK();
     return hipSuccess;
@@ -2400,7 +2496,12 @@ static hipError_t launch_blk_pass(const CycleArgs &a, const BlkArgs &b, int64_t 
     if (err != hipSuccess) return err;
     k_blk_part<PASS, NT><<<wide, NT, sh_hist, st>>>(a, b);
     LAUNCH_CHECK();
-    k_blk_count<PASS><<<wide, BLK_COUNT_THREADS, sh_cnt, st>>>(a, b);
+    if (a.c4) {   // global counts: the block counts are all that is needed
+        k_blk_count<PASS, true><<<wide, BLK_COUNT_THREADS, sh_cnt + c4_lds(a.L), st>>>(a, b);
+        LAUNCH_CHECK();
+        return hipSuccess;
+    }
+    k_blk_count<PASS, false><<<wide, BLK_COUNT_THREADS, sh_cnt, st>>>(a, b);
     LAUNCH_CHECK();
     k_blk_emit<PASS, BLK_EMIT_THREADS><<<wide, BLK_EMIT_THREADS, sh_acc, st>>>(a, b);
     LAUNCH_CHECK();
