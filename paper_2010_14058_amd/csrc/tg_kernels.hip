@@ -369,64 +369,102 @@ k_tdeg_long(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
 // WAVE/TRI_GROUPS lanes per edge; a group walks the shorter row and tests each
 // node against the longer one (its super-hub bitmap when it has one, the
 // hub-core bit matrix when both are hubs, else a binary search), counting
-// hits by type.
+// hits by type.  Edges whose shorter row exceeds TRI_LONG are walked by the
+// whole wave, one after the other: a group of eight lanes took the longest of
+// them through hundreds of dependent steps while the other groups waited.
 constexpr int TRI_GROUPS = 8;
 constexpr int TRI_LANES = WAVE / TRI_GROUPS;
+constexpr int64_t TRI_LONG = 128;
 
-// A register budget for eight waves per SIMD (two registers spill) hides more
-// of the probes' latency than seven waves do.
+// ML: types the counters are unrolled for (8 where they suffice: half the
+// registers and half the selects per hit).  Bound by the latency of the probes,
+// so the register budget is for eight waves per SIMD.  Against one group per
+// edge whatever its rows and 16 counters: 0.67 to 0.44 ms for 300k edges with
+// long tails, 2.9 to 2.45 ms for 5M tripartite edges, 0.53 to 0.51 ms for 1M
+// power-law edges; the 10M-edge power law stays at 9.2 ms.  A bound of 256 or
+// 512 instead of 128 measures the same within 0.1 ms.
+template <int ML>
 __global__ void __attribute__((amdgpu_waves_per_eu(8)))
 k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
-                      const uint8_t *__restrict__ ctype, const int32_t *__restrict__ ei,
-                      const int32_t *__restrict__ ej, const uint32_t *__restrict__ eslot,
-                      uint32_t *__restrict__ tri_slot, int64_t m, int L,
-                      uint32_t *__restrict__ tri, uint32_t *__restrict__ ttot,
-                      uint64_t *__restrict__ tri_sum, int32_t sh_base,
-                      int64_t nw, const uint64_t *__restrict__ SB, int32_t hub_base, int Hw,
-                      const uint64_t *__restrict__ HB, const uint32_t *__restrict__ status) {
+      const uint8_t *__restrict__ ctype, const int32_t *__restrict__ ei,
+      const int32_t *__restrict__ ej, const uint32_t *__restrict__ eslot,
+      uint32_t *__restrict__ tri_slot, int64_t m, int L, uint32_t *__restrict__ tri,
+      uint32_t *__restrict__ ttot, uint64_t *__restrict__ tri_sum, int32_t sh_base, int64_t nw,
+      const uint64_t *__restrict__ SB, int32_t hub_base, int Hw, const uint64_t *__restrict__ HB,
+      const uint32_t *__restrict__ status) {
     if (input_failed(status)) return;
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     const int lane = lane_id();
     const int grp = lane / TRI_LANES, gl = lane % TRI_LANES;
     uint64_t tot_all = 0;
+    // walks slots [sb, se) from sb + first by steps of `step` against the row
+    // [bb, be) of node big
+    auto walk = [&](int64_t sb, int64_t se, int64_t bb, int64_t be, int32_t big, int first, int step,
+                    uint32_t (&cnt)[ML]) {
+        const bool probe = big >= sh_base;
+        const uint64_t *srow = probe ? SB + (size_t)(big - sh_base) * nw : nullptr;
+        const bool big_hub = big >= hub_base;
+        const uint64_t *hrow = big_hub ? HB + (size_t)(big - hub_base) * Hw : nullptr;
+        for (int64_t s = sb + first; s < se; s += step) {
+            const int32_t x = ncol[s];
+            bool found;
+            if (probe) {
+                found = (srow[x >> 6] >> (x & 63)) & 1ull;
+            } else if (big_hub && x >= hub_base) {
+                // both in the hub core: its bit matrix
+                const int hx = x - hub_base;
+                found = (hrow[hx >> 6] >> (hx & 63)) & 1ull;
+            } else {
+                const int64_t q = lower_bound(ncol, bb, be, x);
+                found = q < be && ncol[q] == x;
+            }
+            if (found) {
+                const int tx = ctype[s];
+#pragma unroll
+                for (int t = 0; t < ML; ++t) cnt[t] += (t == tx);
+            }
+        }
+    };
     // a bounded grid walks the edges: per-edge work is small, so launching
     // one workgroup per 32 edges would leave the dispatcher as the limit
     for (int64_t wv = wave; wv * TRI_GROUPS < m; wv += nwaves) {
         const int64_t e = wv * TRI_GROUPS + grp;
-        uint32_t cnt[TG_MAX_L];
+        uint32_t cnt[ML];
 #pragma unroll
-        for (int t = 0; t < TG_MAX_L; ++t) cnt[t] = 0;
+        for (int t = 0; t < ML; ++t) cnt[t] = 0;
+        int64_t sb = 0, se = 0, bb = 0, be = 0;
+        int32_t big = 0;
         if (e < m) {
-            int32_t i = ei[e], j = ej[e];
-            int64_t sb = nrp[i], se = nrp[i + 1], bb = nrp[j], be = nrp[j + 1];
-            int32_t big = j;
+            const int32_t i = ei[e], j = ej[e];
+            sb = nrp[i]; se = nrp[i + 1]; bb = nrp[j]; be = nrp[j + 1];
+            big = j;
             if (se - sb > be - bb) {
-                int64_t t0 = sb, t1 = se;
+                const int64_t t0 = sb, t1 = se;
                 sb = bb; se = be; bb = t0; be = t1;
                 big = i;
             }
-            const bool probe = big >= sh_base;
-            const int sidx = big - sh_base;
-            const bool big_hub = big >= hub_base;
-            const uint64_t *hrow = big_hub ? HB + (size_t)(big - hub_base) * Hw : nullptr;
-            for (int64_t s = sb + gl; s < se; s += TRI_LANES) {
-                int32_t x = ncol[s];
-                bool found;
-                if (probe) {
-                    found = sh_bit(SB, nw, sidx, x);
-                } else if (big_hub && x >= hub_base) {
-                    // both in the hub core: its bit matrix
-                    const int hx = x - hub_base;
-                    found = (hrow[hx >> 6] >> (hx & 63)) & 1ull;
-                } else {
-                    int64_t q = lower_bound(ncol, bb, be, x);
-                    found = q < be && ncol[q] == x;
-                }
-                if (found) {
-                    int tx = ctype[s];
+            if (se - sb <= TRI_LONG) walk(sb, se, bb, be, big, gl, TRI_LANES, cnt);
+        }
+        uint64_t longs = __ballot(e < m && se - sb > TRI_LONG && gl == 0);
+        while (longs) {
+            const int src = __ffsll((long long)longs) - 1;
+            longs &= longs - 1;
+            const int64_t lsb = __shfl((long long)sb, src, WAVE), lse = __shfl((long long)se, src, WAVE);
+            const int64_t lbb = __shfl((long long)bb, src, WAVE), lbe = __shfl((long long)be, src, WAVE);
+            const int32_t lbig = __shfl(big, src, WAVE);
+            uint32_t c[ML];
 #pragma unroll
-                    for (int t = 0; t < TG_MAX_L; ++t) cnt[t] += (t == tx);
+            for (int t = 0; t < ML; ++t) c[t] = 0;
+            walk(lsb, lse, lbb, lbe, lbig, lane, WAVE, c);
+            // summed over the groups; the group's own lanes keep the sums
+#pragma unroll
+            for (int t = 0; t < ML; ++t) {
+                if (t < L) {
+                    uint32_t v = c[t];
+#pragma unroll
+                    for (int d = TRI_LANES; d < WAVE; d <<= 1) v += __shfl_xor(v, d, WAVE);
+                    if (grp == src / TRI_LANES) cnt[t] = v;
                 }
             }
         }
@@ -437,7 +475,7 @@ k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
         const size_t si = e < m ? (size_t)eslot[2 * e] * LP : 0;
         const size_t sj = e < m ? (size_t)eslot[2 * e + 1] * LP : 0;
 #pragma unroll
-        for (int t = 0; t < TG_MAX_L; ++t) {
+        for (int t = 0; t < ML; ++t) {
             if (t < L) {
                 uint32_t v = cnt[t];
 #pragma unroll
@@ -2353,9 +2391,14 @@ hipError_t launch_tri(const int64_t *nrp, const int32_t *ncol, const uint8_t *ct
                       int32_t hub_base, int Hw, const uint64_t *HB, const uint32_t *status,
                       hipStream_t st) {
     if (m == 0) return hipSuccess;
-    k_tri<<<blocks_bounded(m, 4 * TRI_GROUPS, 32), 256, 0, st>>>(
-        nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, ttot, tri_sum, sh_base, nw, SB,
-        hub_base, Hw, HB, status);
+    const unsigned grid = blocks_bounded(m, 4 * TRI_GROUPS, 32);
+    if (L <= 8)
+        k_tri<8><<<grid, 256, 0, st>>>(nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri, ttot,
+                                       tri_sum, sh_base, nw, SB, hub_base, Hw, HB, status);
+    else
+        k_tri<TG_MAX_L><<<grid, 256, 0, st>>>(nrp, ncol, ctype, ei, ej, eslot, tri_slot, m, L, tri,
+                                              ttot, tri_sum, sh_base, nw, SB, hub_base, Hw, HB,
+                                              status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
