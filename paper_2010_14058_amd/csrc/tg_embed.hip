@@ -42,7 +42,19 @@ namespace {
 
 constexpr int EMB_MAX_P = 256;     // largest block (dim + oversample)
 constexpr int DENSE_MAX = 64;      // largest component solved densely in LDS
-constexpr int GRAM_ROWS = 2048;    // rows per Gram partial
+constexpr int64_t GRAM_ROWS = 2048;    // most rows per Gram or residual partial
+constexpr int64_t GRAM_STEP = 32;      // rows are a multiple of a staged step
+constexpr int64_t GRAM_CHUNKS = 256;   // partials aimed at: one workgroup per CU
+
+// Rows per partial of an s-row block: as many as leave GRAM_CHUNKS partials,
+// within the bounds above.  At 2048 rows whatever the size, the 6,968-row
+// component of a 20k-node graph had four workgroups: 267 us per Gram product
+// and 184 us per residual, against 6.9 and under 7 us with 32 rows.
+inline int64_t gram_rows(int64_t s) {
+    int64_t r = (s + GRAM_CHUNKS - 1) / GRAM_CHUNKS;
+    r = (r + GRAM_STEP - 1) / GRAM_STEP * GRAM_STEP;
+    return r < GRAM_STEP ? GRAM_STEP : r > GRAM_ROWS ? GRAM_ROWS : r;
+}
 
 // ------------------------------------------------------ edge weights
 
@@ -291,7 +303,11 @@ __global__ void k_emb_widen(const double *__restrict__ X, int64_t s, int p, int 
 // by every product: local row r is node nodes[r], only nonzero entries,
 // columns as local rows.  A row of more than SPMM_CH nonzeros (a hub) is
 // cut into items of SPMM_CH, each a wave's work in the products.
-constexpr int SPMM_CH = 512;
+// A wave's nonzeros are a serial chain, so the longest item or row sets the
+// product's time: 126 us (rows 56, items 70) on the 6,968-row component of a
+// 20k-node power law with 512 and two nonzeros in flight, 25 us (13, 12) with
+// 128 and four.
+constexpr int SPMM_CH = 128;
 
 __global__ void k_loc_len(const int64_t *__restrict__ rp, const double *__restrict__ wslot,
                           const uint32_t *__restrict__ nodes, int64_t ns, int64_t *__restrict__ len,
@@ -361,20 +377,28 @@ __device__ __forceinline__ void spmm_range(const int32_t *__restrict__ lcol,
 #pragma unroll
     for (int c = 0; c < CPL; ++c) acc[c] = 0.0;
     int64_t k = k0 + g;
-    for (; k + NG < k1; k += 2 * NG) {
-        const int32_t c0 = lcol[k], c1 = lcol[k + NG];
-        const double v0 = lval[k], v1 = lval[k + NG];
-        const double *x0 = X + (size_t)c0 * p, *x1 = X + (size_t)c1 * p;
+    // four nonzeros in flight, added in order
+    for (; k + 3 * NG < k1; k += 4 * NG) {
+        const double *x[4];
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = X + (size_t)lcol[k + u * NG] * p;
+            v[u] = lval[k + u * NG];
+        }
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
             const int j = li + c * GS;
             if (j < p) {
-                acc[c] += v0 * x0[j];
-                acc[c] += v1 * x1[j];
+                double y[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) y[u] = x[u][j];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[c] += v[u] * y[u];
             }
         }
     }
-    if (k < k1) {
+    for (; k < k1; k += NG) {
         const double v0 = lval[k];
         const double *x0 = X + (size_t)lcol[k] * p;
 #pragma unroll
@@ -458,6 +482,7 @@ k_spmm_finish(const int64_t *__restrict__ hptr, int64_t ns, int p, const double 
         if (i0 == i1) continue;
         for (int j = lane; j < p; j += WAVE) {
             double acc = 0.0;
+#pragma unroll 8
             for (int64_t i = i0; i < i1; ++i) acc += part[(size_t)i * p + j];
             const size_t o = (size_t)r * p + j;
             double v = alpha * acc + beta * X[o];
@@ -488,7 +513,7 @@ constexpr int MK = 32;     // depth staged in LDS per step
 // fed to the fp64 matrix cores, the rows being the contraction index.
 __global__ void __launch_bounds__(256)
 k_emb_gram_part(const double *__restrict__ A, const double *__restrict__ B, int64_t n, int p,
-                double *__restrict__ part) {
+                int64_t rows, double *__restrict__ part) {
     __shared__ double as[MK][MT + 1];
     __shared__ double bs[MK][MT + 1];
     // blockIdx.y enumerates the tiles (ti, tj) with ti <= tj: the products
@@ -500,8 +525,8 @@ k_emb_gram_part(const double *__restrict__ A, const double *__restrict__ B, int6
         ++ti;
     }
     const int i0 = ti * MT, j0 = (ti + rest) * MT;
-    const int64_t r0 = (int64_t)blockIdx.x * GRAM_ROWS;
-    const int64_t r1 = r0 + GRAM_ROWS < n ? r0 + GRAM_ROWS : n;
+    const int64_t r0 = (int64_t)blockIdx.x * rows;
+    const int64_t r1 = r0 + rows < n ? r0 + rows : n;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
     dbl4 acc[4];
 #pragma unroll
@@ -532,18 +557,40 @@ k_emb_gram_part(const double *__restrict__ A, const double *__restrict__ B, int6
         }
 }
 
-// C = sum of the partials, chunk by chunk in order (a fixed order: the same
-// inputs give the same bits); an entry below the diagonal in a tile below
-// the diagonal tiles takes its mirror image.
-__global__ void k_emb_gram_sum(const double *__restrict__ part, int64_t chunks, int p,
-                               double *__restrict__ C) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= p * p) return;
+// Sum of column q of `chunks` partials of `pitch` words each, by the
+// SUM_LANES threads (threadIdx.x / SUM_COLS) of a column, each over every
+// SUM_LANES-th partial, then over the threads in order (a fixed order: the
+// same inputs give the same bits).  Thread threadIdx.x < SUM_COLS returns it.
+constexpr int SUM_COLS = 32;
+constexpr int SUM_LANES = 256 / SUM_COLS;
+
+__device__ __forceinline__ double chunk_sum(const double *__restrict__ part, int64_t chunks,
+                                            int64_t pitch, int64_t q, bool in) {
+    __shared__ double red[SUM_LANES][SUM_COLS];
+    const int col = threadIdx.x % SUM_COLS, g = threadIdx.x / SUM_COLS;
+    double s = 0.0;
+    if (in) {
+#pragma unroll 8
+        for (int64_t c = g; c < chunks; c += SUM_LANES) s += part[c * pitch + q];
+    }
+    red[g][col] = s;
+    __syncthreads();
+    s = 0.0;
+    if (g == 0)
+        for (int x = 0; x < SUM_LANES; ++x) s += red[x][col];
+    return s;
+}
+
+// C = sum of the partials; an entry below the diagonal in a tile below the
+// diagonal tiles takes its mirror image.
+__global__ void __launch_bounds__(256)
+k_emb_gram_sum(const double *__restrict__ part, int64_t chunks, int p, double *__restrict__ C) {
+    const int q = blockIdx.x * SUM_COLS + threadIdx.x % SUM_COLS;
+    const bool in = q < p * p;
     const int i = q / p, j = q % p;
     const int src = (i / MT > j / MT) ? j * p + i : q;
-    double s = 0.0;
-    for (int64_t c = 0; c < chunks; ++c) s += part[(size_t)c * p * p + src];
-    C[q] = s;
+    const double s = chunk_sum(part, chunks, (int64_t)p * p, src, in);
+    if (in && threadIdx.x < SUM_COLS) C[q] = s;
 }
 
 // ----------------------------------------------- small symmetric eigen
@@ -983,7 +1030,7 @@ k_emb_apply(const double *__restrict__ X, const double *__restrict__ Q, int64_t 
 // summed: one wave per row range.
 __global__ void __launch_bounds__(256)
 k_emb_residual_part(const double *__restrict__ X, const double *__restrict__ MX,
-                    const double *__restrict__ theta, int64_t n, int p,
+                    const double *__restrict__ theta, int64_t n, int p, int64_t rows,
                     double *__restrict__ part) {
     constexpr int CPL = EMB_MAX_P / WAVE;
     const int lane = lane_id();
@@ -992,8 +1039,8 @@ k_emb_residual_part(const double *__restrict__ X, const double *__restrict__ MX,
     double acc[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) acc[c] = 0.0;
-    const int64_t r0 = (int64_t)blockIdx.x * GRAM_ROWS;
-    const int64_t r1 = r0 + GRAM_ROWS < n ? r0 + GRAM_ROWS : n;
+    const int64_t r0 = (int64_t)blockIdx.x * rows;
+    const int64_t r1 = r0 + rows < n ? r0 + rows : n;
     for (int64_t r = r0 + w; r < r1; r += 4) {
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
@@ -1014,13 +1061,12 @@ k_emb_residual_part(const double *__restrict__ X, const double *__restrict__ MX,
         part[(size_t)blockIdx.x * p + j] = red[0][j] + red[1][j] + red[2][j] + red[3][j];
 }
 
-__global__ void k_emb_residual_sum(const double *__restrict__ part, int64_t chunks, int p,
-                                   double *__restrict__ res) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= p) return;
-    double s = 0.0;
-    for (int64_t c = 0; c < chunks; ++c) s += part[(size_t)c * p + j];
-    res[j] = sqrt(s);
+__global__ void __launch_bounds__(256)
+k_emb_residual_sum(const double *__restrict__ part, int64_t chunks, int p,
+                   double *__restrict__ res) {
+    const int j = blockIdx.x * SUM_COLS + threadIdx.x % SUM_COLS;
+    const double s = chunk_sum(part, chunks, p, j, j < p);
+    if (j < p && threadIdx.x < SUM_COLS) res[j] = sqrt(s);
 }
 
 // Z[nodes[r]][0..dim) = X[r][0..dim) / its length (unscaled when raw);
@@ -1058,7 +1104,10 @@ EmbLayout emb_layout(int64_t n, int64_t nnz, int dim) {
     y.p0 = p;
     y.pmax = 4 * p < EMB_MAX_P ? 4 * p : EMB_MAX_P;
     const int pm = y.pmax;
-    y.chunks = (n + GRAM_ROWS - 1) / GRAM_ROWS;
+    // a component of at most n rows has at most as many partials
+    y.chunks = (n + GRAM_STEP - 1) / GRAM_STEP;
+    if (y.chunks > GRAM_CHUNKS) y.chunks = GRAM_CHUNKS;
+    if (y.chunks < (n + GRAM_ROWS - 1) / GRAM_ROWS) y.chunks = (n + GRAM_ROWS - 1) / GRAM_ROWS;
     if (y.chunks < 1) y.chunks = 1;
     // a row of more than SPMM_CH nonzeros has at most twice len / SPMM_CH items
     y.max_items = 2 * (nnz / SPMM_CH) + 1;
@@ -1311,7 +1360,8 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
         const int pcap = (int)(ns < y.pmax ? ns : y.pmax);
         int p = (int)(ns < p0 ? ns : p0);
         const int want = dim < p ? dim : p;
-        const int64_t chunks = (ns + GRAM_ROWS - 1) / GRAM_ROWS;
+        const int64_t grows = gram_rows(ns), chunks = (ns + grows - 1) / grows;
+        if (chunks > y.chunks) return TG_E_INTERNAL;
         // flops of an s x p by p x p product, and of a symmetric Gram product
         // (one triangle)
         auto dense_flops = [&]() { return 2.0 * (double)ns * (double)p * (double)p; };
@@ -1320,9 +1370,10 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
             const int mt = (p + MT - 1) / MT;
             ksum_begin(st);
             k_emb_gram_part<<<dim3((unsigned)chunks, (unsigned)(mt * (mt + 1) / 2)), 256, 0, st>>>(
-                A, B, ns, p, part);
+                A, B, ns, p, grows, part);
             ksum_end("gram", gram_flops(), st);
-            k_emb_gram_sum<<<(unsigned)((p * p + 255) / 256), 256, 0, st>>>(part, chunks, p, C);
+            k_emb_gram_sum<<<(unsigned)((p * p + SUM_COLS - 1) / SUM_COLS), 256, 0, st>>>(part, chunks,
+                                                                                       p, C);
             return hipGetLastError();
         };
         auto apply = [&](const double *A, const double *Q, double *out) -> hipError_t {
@@ -1400,8 +1451,10 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
             if ((e = hipMemcpyAsync(theta, sigma, sizeof(double) * p, hipMemcpyDeviceToDevice,
                                     st)) != hipSuccess)
                 return e;
-            k_emb_residual_part<<<(unsigned)chunks, 256, 0, st>>>(xo, mo, theta, ns, p, part);
-            k_emb_residual_sum<<<1, 256, 0, st>>>(part, chunks, p, res);
+            k_emb_residual_part<<<(unsigned)chunks, 256, 0, st>>>(xo, mo, theta, ns, p, grows,
+                                                                   part);
+            k_emb_residual_sum<<<(unsigned)((p + SUM_COLS - 1) / SUM_COLS), 256, 0, st>>>(
+                part, chunks, p, res);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if ((e = hipMemcpyAsync(h_theta.data(), theta, sizeof(double) * p,
                                     hipMemcpyDeviceToHost, st)) != hipSuccess)
