@@ -21,7 +21,8 @@
  *   means the null stream).  The call synchronises that stream once during
  *   the input checks (twice for a batch) and once at the end, to read back
  *   the device-side checks, so the counts are complete when it returns
- *   (tg_count_batch_async: never).
+ *   (a graph of few edges: once in all, or once more when it is found too
+ *   long to count edge by edge; tg_count_batch_async: never).
  * Errors: every call returns tg_status.  Input checks run before any output
  *   is written; on an input error the outputs are left untouched.  Device
  *   faults reported by HIP map to TG_E_DEVICE; a failed internal check
@@ -627,6 +628,8 @@ int32_t tg_phase_times(float *ms, const char **names, int32_t max_phases);
  * (the rest of [8] is probed by binary search), [10] hub-core size,
  * [11] groups on the blocked cycle path (both passes), [12] pass-A wedges
  * in blocked groups, [13] pass-B wedges in blocked groups.
+ * A path that skips a stage (graphs of few edges, batches of small graphs,
+ * global counts without per-edge rows) reports 0 for what it did not run.
  * Returns the number written (at most TG_NUM_STATS). */
 #define TG_NUM_STATS 14
 int32_t tg_last_stats(int64_t *stats, int32_t max_stats);
