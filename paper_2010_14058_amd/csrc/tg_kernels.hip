@@ -378,13 +378,14 @@ constexpr int64_t TRI_LONG = 128;
 
 // ML: types the counters are unrolled for (8 where they suffice: half the
 // registers and half the selects per hit).  Bound by the latency of the probes,
-// so the register budget is for eight waves per SIMD.  Against one group per
-// edge whatever its rows and 16 counters: 0.67 to 0.44 ms for 300k edges with
-// long tails, 2.9 to 2.45 ms for 5M tripartite edges, 0.53 to 0.51 ms for 1M
-// power-law edges; the 10M-edge power law stays at 9.2 ms.  A bound of 256 or
-// 512 instead of 128 measures the same within 0.1 ms.
+// so the register budget is for eight waves per SIMD (six with sixteen types,
+// where eight spill 26 registers: 0.92 to 0.88 ms for 1M edges).  Against one
+// group per edge whatever its rows and 16 counters: 0.67 to 0.44 ms for 300k
+// edges with long tails, 2.9 to 2.45 ms for 5M tripartite edges, 0.53 to 0.51 ms
+// for 1M power-law edges; the 10M-edge power law stays at 9.2 ms.  A bound of
+// 256 or 512 instead of 128 measures the same within 0.1 ms.
 template <int ML>
-__global__ void __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __attribute__((amdgpu_waves_per_eu(ML <= 8 ? 8 : 6)))
 k_tri(const int64_t *__restrict__ nrp, const int32_t *__restrict__ ncol,
       const uint8_t *__restrict__ ctype, const int32_t *__restrict__ ei,
       const int32_t *__restrict__ ej, const uint32_t *__restrict__ eslot,
