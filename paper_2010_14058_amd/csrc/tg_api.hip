@@ -314,7 +314,8 @@ void timing_mark(const char *name) {
 static tg_status status_from_bits(uint32_t bits) {
     if (bits & (ST_BATCH | ST_CROSS_GRAPH)) return TG_E_BATCH;
     if (bits & ST_TYPE_RANGE) return TG_E_TYPE_RANGE;
-    if (bits & (ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_ASYMMETRIC | ST_EDGE_COUNT))
+    if (bits & (ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_ASYMMETRIC | ST_EDGE_COUNT |
+                ST_ROW_BOUNDS))
         return TG_E_NOT_SIMPLE;
     if (bits) return TG_E_INTERNAL;
     return TG_OK;

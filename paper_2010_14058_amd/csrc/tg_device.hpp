@@ -91,6 +91,15 @@ static __device__ __forceinline__ bool input_failed(const uint32_t *status) {
     return (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ST_INPUT) != 0;
 }
 
+// The same for a check kernel whose workgroups meet at barriers: only the bits
+// that it does not raise itself (`raised`) count.  Its other workgroups set
+// those while it runs, and a wave that returned on one would leave the rest of
+// its workgroup with shared memory that it should have filled.
+static __device__ __forceinline__ bool failed_before(const uint32_t *status, uint32_t raised) {
+    return (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ST_INPUT &
+            ~raised) != 0;
+}
+
 // C(n, r) for r <= 4 (co-lexicographic ranks of type multisets).
 static __device__ __forceinline__ int64_t binom_small(int64_t n, int r) {
     if (n < r) return 0;

@@ -47,7 +47,7 @@ k_dir_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
         const int64_t b = rp[u], e = rp[u + 1];
         int64_t up = 0;
         if (b < 0 || e < b || e > nnz || (u == 0 && b != 0) || (u == n - 1 && e != nnz)) {
-            bad = ST_UNSORTED;
+            bad = ST_ROW_BOUNDS;
         } else {
             if (types[u] >= L) bad |= ST_TYPE_RANGE;
             up = e - upper_bound(col, b, e, (int32_t)u);
@@ -76,8 +76,8 @@ k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             uint32_t *__restrict__ status) {
     __shared__ SlotTile T;
     __shared__ uint32_t cnt[DIR_TILE_WORDS];
+    if (failed_before(status, ST_COL_RANGE | ST_SELF_LOOP | ST_UNSORTED | ST_ASYMMETRIC)) return;
     uint64_t own = 0;
-    if (load_agent(status) != 0) return;
     const int tid = threadIdx.x, C = 3 * L;
     uint32_t bad = 0;
     for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;

@@ -22,13 +22,15 @@ enum : uint32_t {
     ST_BATCH = 1u << 7,       // inconsistent batch descriptor
     ST_CROSS_GRAPH = 1u << 8, // an edge joins two graphs of a batch
     ST_EDGE_COUNT = 1u << 9,  // entries above the diagonal are not half the adjacency
+    ST_ROW_BOUNDS = 1u << 10, // row offsets decrease or leave [0, nnz]
 };
 
 // Bits that mean the input is unusable: every kernel after the input checks
 // returns at once when one is set (so a call that never reads the status
 // back on the host stays in bounds).
 constexpr uint32_t ST_INPUT = ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_TYPE_RANGE |
-                              ST_ASYMMETRIC | ST_BATCH | ST_CROSS_GRAPH | ST_EDGE_COUNT;
+                              ST_ASYMMETRIC | ST_BATCH | ST_CROSS_GRAPH | ST_EDGE_COUNT |
+                              ST_ROW_BOUNDS;
 
 // Tunables of the cycle and clique passes.
 constexpr int64_t SMALL_WEDGES = 128; // light groups of the small table

@@ -46,7 +46,7 @@ k_check_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
         if (u == 0) ucount[n] = 0;  // sentinel of the exclusive scan
         const int64_t b = rp[u], e = rp[u + 1];
         if (b < 0 || e > nnz || e < b || (u == 0 && b != 0) || (u == n - 1 && e != nnz)) {
-            bad = ST_UNSORTED;
+            bad = ST_ROW_BOUNDS;
             deg[u] = 0;
             ucount[u] = 0;
         } else {
@@ -67,7 +67,7 @@ k_check_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, i
               int64_t nnz, uint32_t *__restrict__ status,
               const int32_t *__restrict__ node_graph) {
     __shared__ SlotTile T;
-    if (input_failed(status)) return;
+    if (failed_before(status, ST_COL_RANGE | ST_CROSS_GRAPH | ST_SELF_LOOP | ST_UNSORTED)) return;
     uint32_t bad = 0;
     for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
          s0 += (int64_t)gridDim.x * SLOT_TILE) {
@@ -238,7 +238,7 @@ k_slot_keys(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int32_t *__restrict__ ei,
             int32_t *__restrict__ ej, uint32_t *__restrict__ status) {
     __shared__ SlotTile T;
-    if (input_failed(status)) return;  // includes an edge count that is not nnz / 2
+    if (failed_before(status, ST_ASYMMETRIC)) return;  // includes an edge count that is not nnz / 2
     uint32_t bad = 0;
     for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
          s0 += (int64_t)gridDim.x * SLOT_TILE) {
@@ -2268,7 +2268,8 @@ __global__ void k_status_code(const uint32_t *__restrict__ status, int32_t *__re
     tg_status s = TG_OK;
     if (b & (ST_BATCH | ST_CROSS_GRAPH)) s = TG_E_BATCH;
     else if (b & ST_TYPE_RANGE) s = TG_E_TYPE_RANGE;
-    else if (b & (ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_ASYMMETRIC | ST_EDGE_COUNT))
+    else if (b & (ST_COL_RANGE | ST_UNSORTED | ST_SELF_LOOP | ST_ASYMMETRIC | ST_EDGE_COUNT |
+                  ST_ROW_BOUNDS))
         s = TG_E_NOT_SIMPLE;
     else if (b) s = TG_E_INTERNAL;
     *out = (int32_t)s;

@@ -105,7 +105,7 @@ k_small_check(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
               const uint64_t *__restrict__ counters, int c_count, int max_nodes, int64_t n_all,
               int64_t nnz, uint32_t *__restrict__ status) {
     extern __shared__ unsigned long long sm_check[];
-    if (input_failed(status)) return;
+    if (failed_before(status, ST_INPUT & ~ST_BATCH)) return;
     unsigned long long *bits = sm_check;
     uint32_t *row = reinterpret_cast<uint32_t *>(bits + (size_t)max_nodes * small_stride(max_nodes));
     const int tid = threadIdx.x;
