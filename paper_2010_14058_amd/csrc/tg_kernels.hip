@@ -39,7 +39,9 @@ k_check_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
               uint32_t *__restrict__ deg, int64_t *__restrict__ ucount,
               uint32_t *__restrict__ status, const int32_t *__restrict__ node_graph,
               const int32_t *__restrict__ gL) {
-    if (input_failed(status)) return;  // inconsistent batch descriptor
+    // an inconsistent batch descriptor; this launch's own findings stop no row,
+    // so that every error of the input is known to the status code
+    if (failed_before(status, ST_ROW_BOUNDS | ST_TYPE_RANGE)) return;
     const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
     uint32_t bad = 0;
     if (u < n) {
@@ -59,7 +61,8 @@ k_check_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
     if (lane_id() == 0 && bad) atomicOr(status, bad);
 }
 
-// The rows' entries, one per thread (rows bounds are valid here).  A wave per
+// The rows' entries, one per thread (rows bounds are valid here; a type out of
+// range must not hide an edge between two graphs of a batch).  A wave per
 // row took 0.72 ms on the 10M-edge power law, all but 0.1 ms of it waiting for
 // the wave of its 53,000-neighbour hub.
 __global__ void __launch_bounds__(256)
@@ -67,7 +70,9 @@ k_check_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, i
               int64_t nnz, uint32_t *__restrict__ status,
               const int32_t *__restrict__ node_graph) {
     __shared__ SlotTile T;
-    if (failed_before(status, ST_COL_RANGE | ST_CROSS_GRAPH | ST_SELF_LOOP | ST_UNSORTED)) return;
+    if (failed_before(status, ST_COL_RANGE | ST_CROSS_GRAPH | ST_SELF_LOOP | ST_UNSORTED |
+                                  ST_TYPE_RANGE))
+        return;
     uint32_t bad = 0;
     for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
          s0 += (int64_t)gridDim.x * SLOT_TILE) {

@@ -97,7 +97,9 @@ __device__ __forceinline__ int small_row(const uint32_t *row, int n, uint32_t s)
 }
 
 // Input checks of every graph (the batch descriptor has passed its own):
-// rows, types, and the symmetry of the adjacency from its bit matrix.
+// rows, types, and the symmetry of the adjacency from its bit matrix.  Only row
+// offsets out of order stop a graph's other checks, and no graph those of
+// another, so that the status code knows every error.
 __global__ void __launch_bounds__(SMALL_THREADS)
 k_small_check(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
               const uint8_t *__restrict__ types, const int64_t *__restrict__ node_ptr,
@@ -123,17 +125,17 @@ k_small_check(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             // offsets from the graph's first slot; a graph of n nodes has
             // fewer than n^2 slots
             const int64_t o = e - s0;
-            if (s0 < 0 || o < 0 || e > nnz || o > (int64_t)n * n) bad |= ST_UNSORTED;
+            if (s0 < 0 || o < 0 || e > nnz || o > (int64_t)n * n) bad |= ST_ROW_BOUNDS;
             row[v] = (uint32_t)o;
             if (v < n) {
-                if (rp[a + v + 1] < e) bad |= ST_UNSORTED;
+                if (rp[a + v + 1] < e) bad |= ST_ROW_BOUNDS;
                 if (types[a + v] >= gL[g]) bad |= ST_TYPE_RANGE;
             }
         }
         if (tid == 0 && ((a == 0 && s0 != 0) || (a + n == n_all && rp[n_all] != nnz)))
-            bad |= ST_UNSORTED;
+            bad |= ST_ROW_BOUNDS;
         for (int q = tid; q < n * stride; q += SMALL_THREADS) bits[q] = 0ull;
-        if (__syncthreads_or(bad != 0)) {
+        if (__syncthreads_or((bad & ST_ROW_BOUNDS) != 0)) {
             if (bad) atomicOr(status, bad);
             continue;
         }

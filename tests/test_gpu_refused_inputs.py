@@ -163,3 +163,21 @@ def test_batch(kind, rows):
     P.count_batch_async(plan, out, status, ws, torch.cuda.current_stream(), out_rows=out_rows)
     torch.cuda.synchronize()
     assert int(status.item()) == want
+
+
+@pytest.mark.parametrize("rows", [False, True], ids=["small", "general"])
+@pytest.mark.parametrize("G", [4, 4000])
+def test_batch_error_order(G, rows):
+    """An edge between two graphs is reported before a type out of range,
+    whichever graph has which."""
+    import paper_2010_14058_amd as P
+
+    for typed in (0, 1, 2, G - 1):
+        arrays, node_ptr, _ = _batch_of_rings("none", G, 24, 4)
+        rp, col, types = arrays
+        types[typed * 24 + 5] = 3
+        col[1 * 24 * 8 + 7] = 2 * 24            # graph 1's first node joined to graph 2
+        rp, col, types = _dev((rp, col, types))
+        plan = P.BatchPlan(rp, col, types, node_ptr, np.full(G, 3, np.int32))
+        print(f"[gpu] batch of {G}: a type in graph {typed}, an edge from 1 to 2", flush=True)
+        assert _code(lambda: P.count_batch(plan, per_edge=rows)) == 9
