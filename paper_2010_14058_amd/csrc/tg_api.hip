@@ -484,7 +484,6 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         // the list lengths share their counters with the 4-cycle groups
         HIPCHK(launch_fill_u64(counters, 0, C_B_HEAVY, st));
         HIPCHK(launch_batch_nodes(batch->node_ptr, batch->G, node_graph, status, st));
-        HIPCHK(launch_fill_u64(global_counts, 0, batch->globals_len, st));
     }
     HIPCHK(launch_check_rows(row_ptr, col, types, n, nnz, L, deg, ucount, status, node_graph,
                              batch ? batch->gL : nullptr, st));
@@ -507,6 +506,8 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     const int bits = bits_for(n);
     HIPCHK(launch_slot_keys(row_ptr, col, ucount, eoff, newid, n, nnz, bits, key_a, val_a, ei, ej, status,
                             st));
+    // the last input check is behind: a batch's sums start at zero in the output
+    if (batch) HIPCHK(launch_clear_outputs(global_counts, batch->globals_len, status, st));
     // hub core and super-hubs: single graphs only (in a batch the top ids are
     // not the top degrees); the largest degree sizes the word widths
     uint64_t cand[2] = {0, 0};

@@ -367,6 +367,8 @@ hipError_t radix_sort(uint64_t *keys, uint64_t *keys_tmp, uint32_t *vals, uint32
 
 // Launch wrappers (tg_kernels.hip).
 hipError_t launch_fill_u64(uint64_t *p, uint64_t v, int64_t count, hipStream_t st);
+hipError_t launch_clear_outputs(uint64_t *p, int64_t count, const uint32_t *status,
+                                hipStream_t st);
 hipError_t launch_check_rows(const int64_t *rp, const int32_t *col, const uint8_t *types, int64_t n,
                              int64_t nnz, int L, uint32_t *deg, int64_t *ucount, uint32_t *status,
                              const int32_t *node_graph, const int32_t *gL, hipStream_t st);

@@ -31,6 +31,14 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t count) {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += stride) p[q] = v;
 }
 
+// Clears the outputs of a call whose input checks have passed.
+__global__ void k_clear_outputs(uint64_t *p, int64_t count, const uint32_t *__restrict__ status) {
+    if (input_failed(status)) return;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += stride)
+        p[q] = 0ull;
+}
+
 // One thread per input row: row bounds, type, degree, number of larger
 // neighbours (the row is searched; k_check_slots checks that it is sorted).
 __global__ void __launch_bounds__(256)
@@ -2306,6 +2314,16 @@ hipError_t launch_fill_u64(uint64_t *p, uint64_t v, int64_t count, hipStream_t s
     int64_t b = (count + 255) / 256;
     if (b > 4096) b = 4096;
     k_fill_u64<<<(unsigned)b, 256, 0, st>>>(p, v, count);
+    LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+hipError_t launch_clear_outputs(uint64_t *p, int64_t count, const uint32_t *status,
+                                hipStream_t st) {
+    if (count <= 0) return hipSuccess;
+    int64_t b = (count + 255) / 256;
+    if (b > 4096) b = 4096;
+    k_clear_outputs<<<(unsigned)b, 256, 0, st>>>(p, count, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }

@@ -153,9 +153,9 @@ def test_batch(kind, rows):
     rp, col, types = _dev(arrays)
     plan = P.BatchPlan(rp, col, types, node_ptr, np.full(G, 3, np.int32))
     print(f"[gpu] batch {kind}: G={G} n={plan.n} nnz={plan.nnz} rows={rows}", flush=True)
-    assert _code(lambda: P.count_batch(plan, per_edge=rows)) == want
-    # without a host synchronisation: the status arrives on the device
     out, status = _full((int(plan.goff_host[-1]),)), _full((1,)).to(torch.int32)
+    assert _code(lambda: P.count_batch(plan, per_edge=rows, out_globals=out), out) == want
+    # without a host synchronisation: the status arrives on the device
     ws = P.Workspace("cuda")
     ws.get(P.batch_workspace_bytes(plan.n, plan.nnz, G, plan.L_max))
     out_rows = (torch.empty((plan.nnz // 2, P.row_width(3)), dtype=torch.int64, device="cuda")
@@ -163,6 +163,7 @@ def test_batch(kind, rows):
     P.count_batch_async(plan, out, status, ws, torch.cuda.current_stream(), out_rows=out_rows)
     torch.cuda.synchronize()
     assert int(status.item()) == want
+    assert bool((out == 77).all())
 
 
 @pytest.mark.parametrize("rows", [False, True], ids=["small", "general"])
