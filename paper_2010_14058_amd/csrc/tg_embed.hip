@@ -46,12 +46,14 @@ constexpr int64_t GRAM_ROWS = 2048;    // most rows per Gram or residual partial
 constexpr int64_t GRAM_STEP = 32;      // rows are a multiple of a staged step
 constexpr int64_t GRAM_CHUNKS = 256;   // partials aimed at: one workgroup per CU
 
-// Rows per partial of an s-row block: as many as leave GRAM_CHUNKS partials,
-// within the bounds above.  At 2048 rows whatever the size, the 6,968-row
-// component of a 20k-node graph had four workgroups: 267 us per Gram product
-// and 184 us per residual, against 6.9 and under 7 us with 32 rows.
-inline int64_t gram_rows(int64_t s) {
-    int64_t r = (s + GRAM_CHUNKS - 1) / GRAM_CHUNKS;
+// Rows per partial of an s-row block: as many as leave GRAM_CHUNKS partials, or
+// the `most` that there is room for, within the bounds above.  At 2048 rows
+// whatever the size, the 6,968-row component of a 20k-node graph had four
+// workgroups: 267 us per Gram product and 184 us per residual, against 6.9 and
+// under 7 us with 32 rows.
+inline int64_t gram_rows(int64_t s, int64_t most) {
+    if (most > GRAM_CHUNKS) most = GRAM_CHUNKS;
+    int64_t r = (s + most - 1) / most;
     r = (r + GRAM_STEP - 1) / GRAM_STEP * GRAM_STEP;
     return r < GRAM_STEP ? GRAM_STEP : r > GRAM_ROWS ? GRAM_ROWS : r;
 }
@@ -301,17 +303,19 @@ __global__ void k_emb_widen(const double *__restrict__ X, int64_t s, int p, int 
 
 // The component's own CSR of S = D^{-1/2} W D^{-1/2}, built once and read
 // by every product: local row r is node nodes[r], only nonzero entries,
-// columns as local rows.  A row of more than SPMM_CH nonzeros (a hub) is
-// cut into items of SPMM_CH, each a wave's work in the products.
+// columns as local rows.  A row of more than `ch` nonzeros (a hub) is cut into
+// items of `ch`, each a wave's work in the products: SPMM_CH of them, or twice
+// or four times as many where the items would outnumber the workspace's (many
+// long rows, so the chip is full with longer items as well).
 // A wave's nonzeros are a serial chain, so the longest item or row sets the
 // product's time: 126 us (rows 56, items 70) on the 6,968-row component of a
 // 20k-node power law with 512 and two nonzeros in flight, 25 us (13, 12) with
 // 128 and four.
-constexpr int SPMM_CH = 128;
+constexpr int SPMM_CH = 128, SPMM_CH_MAX = 512;
 
 __global__ void k_loc_len(const int64_t *__restrict__ rp, const double *__restrict__ wslot,
-                          const uint32_t *__restrict__ nodes, int64_t ns, int64_t *__restrict__ len,
-                          int64_t *__restrict__ hcnt) {
+                          const uint32_t *__restrict__ nodes, int64_t ns, int ch,
+                          int64_t *__restrict__ len, int64_t *__restrict__ hcnt) {
     const int lane = lane_id();
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         len[ns] = 0;
@@ -326,7 +330,7 @@ __global__ void k_loc_len(const int64_t *__restrict__ rp, const double *__restri
         c = wave_sum_u64(c);
         if (lane == 0) {
             len[r] = (int64_t)c;
-            hcnt[r] = c > (uint64_t)SPMM_CH ? (int64_t)((c + SPMM_CH - 1) / SPMM_CH) : 0;
+            hcnt[r] = c > (uint64_t)ch ? (int64_t)((c + ch - 1) / ch) : 0;
         }
     }
 }
@@ -413,19 +417,19 @@ __device__ __forceinline__ void spmm_range(const int32_t *__restrict__ lcol,
 }
 
 // out = alpha * (S X) + beta * X + gamma * Zb on the rows of at most
-// SPMM_CH nonzeros, one wave per row.
+// ch nonzeros, one wave per row.
 template <int GS, int CPL>
 __global__ void __launch_bounds__(256)
 k_spmm_rows(const int64_t *__restrict__ lrp, const int32_t *__restrict__ lcol,
-            const double *__restrict__ lval, int64_t ns, int p, const double *__restrict__ X,
-            const double *__restrict__ Zb, double alpha, double beta, double gamma,
-            double *__restrict__ out) {
+            const double *__restrict__ lval, int64_t ns, int ch, int p,
+            const double *__restrict__ X, const double *__restrict__ Zb, double alpha, double beta,
+            double gamma, double *__restrict__ out) {
     const int lane = lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     for (int64_t r = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; r < ns;
          r += nwaves) {
         const int64_t k0 = lrp[r], k1 = lrp[r + 1];
-        if (k1 - k0 > SPMM_CH) continue;
+        if (k1 - k0 > ch) continue;
         double acc[CPL];
         spmm_range<GS, CPL>(lcol, lval, k0, k1, p, X, acc);
         if (lane < GS) {
@@ -448,15 +452,15 @@ template <int GS, int CPL>
 __global__ void __launch_bounds__(256)
 k_spmm_items(const int64_t *__restrict__ lrp, const int32_t *__restrict__ lcol,
              const double *__restrict__ lval, const int64_t *__restrict__ hptr,
-             const int32_t *__restrict__ hrow, int64_t nitems, int p, const double *__restrict__ X,
-             double *__restrict__ part) {
+             const int32_t *__restrict__ hrow, int64_t nitems, int ch, int p,
+             const double *__restrict__ X, double *__restrict__ part) {
     const int lane = lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     for (int64_t i = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; i < nitems;
          i += nwaves) {
         const int32_t r = hrow[i];
-        const int64_t k0 = lrp[r] + (i - hptr[r]) * SPMM_CH;
-        const int64_t k1 = k0 + SPMM_CH < lrp[r + 1] ? k0 + SPMM_CH : lrp[r + 1];
+        const int64_t k0 = lrp[r] + (i - hptr[r]) * ch;
+        const int64_t k1 = k0 + ch < lrp[r + 1] ? k0 + ch : lrp[r + 1];
         double acc[CPL];
         spmm_range<GS, CPL>(lcol, lval, k0, k1, p, X, acc);
         if (lane < GS) {
@@ -1104,13 +1108,12 @@ EmbLayout emb_layout(int64_t n, int64_t nnz, int dim) {
     y.p0 = p;
     y.pmax = 4 * p < EMB_MAX_P ? 4 * p : EMB_MAX_P;
     const int pm = y.pmax;
-    // a component of at most n rows has at most as many partials
-    y.chunks = (n + GRAM_STEP - 1) / GRAM_STEP;
-    if (y.chunks > GRAM_CHUNKS) y.chunks = GRAM_CHUNKS;
-    if (y.chunks < (n + GRAM_ROWS - 1) / GRAM_ROWS) y.chunks = (n + GRAM_ROWS - 1) / GRAM_ROWS;
+    // the partials of the widest block at GRAM_ROWS rows each (more of them
+    // go to an idle block)
+    y.chunks = (n + GRAM_ROWS - 1) / GRAM_ROWS;
     if (y.chunks < 1) y.chunks = 1;
-    // a row of more than SPMM_CH nonzeros has at most twice len / SPMM_CH items
-    y.max_items = 2 * (nnz / SPMM_CH) + 1;
+    // a row of more than c nonzeros has at most twice len / c items
+    y.max_items = 2 * (nnz / SPMM_CH_MAX) + 1;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
@@ -1341,39 +1344,54 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
         const uint32_t *nodes = order + cs;
         const unsigned rg = row_grid(ns);
         // the component's S as its own CSR, and the items of its long rows
-        k_loc_len<<<rg, 256, 0, st>>>(row_ptr, D(y.wslot), nodes, ns, cnt, eoff);
-        EMB_CHK(hipGetLastError());
-        EMB_CHK(launch_excl_scan(cnt, lrp, ns + 1, reinterpret_cast<int64_t *>(w + y.stmp), nullptr, st));
-        EMB_CHK(launch_excl_scan(eoff, hptr, ns + 1, reinterpret_cast<int64_t *>(w + y.stmp), nullptr,
-                                 st));
+        uint32_t root = 0;
+        int64_t nitems = 0, nnz_c = 0;
+        int ch = SPMM_CH;
+        for (;; ch *= 2) {
+            k_loc_len<<<rg, 256, 0, st>>>(row_ptr, D(y.wslot), nodes, ns, ch, cnt, eoff);
+            EMB_CHK(hipGetLastError());
+            EMB_CHK(launch_excl_scan(cnt, lrp, ns + 1, reinterpret_cast<int64_t *>(w + y.stmp), nullptr,
+                                     st));
+            EMB_CHK(launch_excl_scan(eoff, hptr, ns + 1, reinterpret_cast<int64_t *>(w + y.stmp),
+                                     nullptr, st));
+            EMB_CHK(hipMemcpyAsync(&root, nodes, sizeof(root), hipMemcpyDeviceToHost, st));
+            EMB_CHK(hipMemcpyAsync(&nitems, hptr + ns, sizeof(nitems), hipMemcpyDeviceToHost, st));
+            EMB_CHK(hipMemcpyAsync(&nnz_c, lrp + ns, sizeof(nnz_c), hipMemcpyDeviceToHost, st));
+            EMB_CHK(hipStreamSynchronize(st));
+            if (nitems <= y.max_items) break;
+            if (ch >= SPMM_CH_MAX) return TG_E_INTERNAL;
+        }
         k_loc_fill<<<rg, 256, 0, st>>>(row_ptr, col, D(y.wslot), D(y.sc), nodes, loc, ns, lrp, lcol,
                                        lval);
         k_loc_items<<<grid_of(ns), 256, 0, st>>>(hptr, ns, hrow);
         EMB_CHK(hipGetLastError());
-        uint32_t root = 0;
-        int64_t nitems = 0, nnz_c = 0;
-        EMB_CHK(hipMemcpyAsync(&root, nodes, sizeof(root), hipMemcpyDeviceToHost, st));
-        EMB_CHK(hipMemcpyAsync(&nitems, hptr + ns, sizeof(nitems), hipMemcpyDeviceToHost, st));
-        EMB_CHK(hipMemcpyAsync(&nnz_c, lrp + ns, sizeof(nnz_c), hipMemcpyDeviceToHost, st));
-        EMB_CHK(hipStreamSynchronize(st));
-        if (nitems > y.max_items) return TG_E_INTERNAL;
         const int pcap = (int)(ns < y.pmax ? ns : y.pmax);
         int p = (int)(ns < p0 ? ns : p0);
         const int want = dim < p ? dim : p;
-        const int64_t grows = gram_rows(ns), chunks = (ns + grows - 1) / grows;
-        if (chunks > y.chunks) return TG_E_INTERNAL;
+        // Partials go to a block that is idle at the time, or to their own
+        // region where that is the larger (few nodes): room for GRAM_CHUNKS
+        // of them at the starting width of all but the smallest graphs.
+        // Rows per partial and partials at the block's present width:
+        const int64_t own_words = y.chunks * y.pmax * y.pmax, idle_words = n * y.pmax;
+        const int64_t part_words = own_words > idle_words ? own_words : idle_words;
+        auto part_at = [&](double *idle) { return own_words > idle_words ? part : idle; };
+        auto part_rows = [&]() { return gram_rows(ns, part_words / ((int64_t)p * p)); };
+        auto part_chunks = [&]() { return (ns + part_rows() - 1) / part_rows(); };
         // flops of an s x p by p x p product, and of a symmetric Gram product
         // (one triangle)
         auto dense_flops = [&]() { return 2.0 * (double)ns * (double)p * (double)p; };
         auto gram_flops = [&]() { return (double)ns * (double)p * (double)(p + 1); };
-        auto gram = [&](const double *A, const double *B, double *C) -> hipError_t {
+        auto gram = [&](const double *A, const double *B, double *C, double *idle) -> hipError_t {
             const int mt = (p + MT - 1) / MT;
+            const int64_t chunks = part_chunks();
+            double *parts = part_at(idle);
+            if (chunks * p * p > part_words) return hipErrorInvalidValue;
             ksum_begin(st);
             k_emb_gram_part<<<dim3((unsigned)chunks, (unsigned)(mt * (mt + 1) / 2)), 256, 0, st>>>(
-                A, B, ns, p, grows, part);
+                A, B, ns, p, part_rows(), parts);
             ksum_end("gram", gram_flops(), st);
-            k_emb_gram_sum<<<(unsigned)((p * p + SUM_COLS - 1) / SUM_COLS), 256, 0, st>>>(part, chunks,
-                                                                                       p, C);
+            k_emb_gram_sum<<<(unsigned)((p * p + SUM_COLS - 1) / SUM_COLS), 256, 0, st>>>(
+                parts, chunks, p, C);
             return hipGetLastError();
         };
         auto apply = [&](const double *A, const double *Q, double *out) -> hipError_t {
@@ -1395,11 +1413,11 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
             ksum_begin(st);
 #define EMB_SPMM(GSV, CPLV)                                                                       \
     do {                                                                                          \
-        k_spmm_rows<GSV, CPLV><<<rg, 256, 0, st>>>(lrp, lcol, lval, ns, p, A, Zb, alpha, beta,     \
+        k_spmm_rows<GSV, CPLV><<<rg, 256, 0, st>>>(lrp, lcol, lval, ns, ch, p, A, Zb, alpha, beta, \
                                                    gamma, out);                                   \
         if (nitems)                                                                               \
             k_spmm_items<GSV, CPLV><<<row_grid(nitems), 256, 0, st>>>(lrp, lcol, lval, hptr, hrow, \
-                                                                      nitems, p, A, spart);       \
+                                                                      nitems, ch, p, A, spart);   \
     } while (0)
             if (p <= 16) EMB_SPMM(16, 1);
             else if (p <= 32) EMB_SPMM(32, 1);
@@ -1413,9 +1431,9 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
             ksum_end("spmm", spmm_bytes(Zb != nullptr), st);
             return hipGetLastError();
         };
-        // Cholesky QR: out = A R^{-1}, A^T A = R^T R
+        // Cholesky QR: out = A R^{-1}, A^T A = R^T R (out is idle until then)
         auto orth = [&](const double *A, double *out) -> hipError_t {
-            hipError_t e = gram(A, A, G);
+            hipError_t e = gram(A, A, G, out);
             if (e != hipSuccess) return e;
             ksum_begin(st);
             if (p <= LDS_P) k_emb_chol_lds<<<1, 1024, 0, st>>>(G, Vs, p);
@@ -1430,13 +1448,13 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
         std::vector<double> h_theta, h_res;
         // Rayleigh-Ritz on the orthonormal block Q: Ritz vectors to xo, M
         // times them to mo, Ritz values to theta (descending), residual
-        // norms read back.
+        // norms read back (Yp is idle).
         auto rayleigh_ritz = [&](const double *Q, double *xo, double *mo) -> hipError_t {
             hipError_t e;
             h_theta.assign((size_t)p, 0.0);
             h_res.assign((size_t)p, 0.0);
             if ((e = spmm(Q, nullptr, 0.5, 0.5, 0.0, MX)) != hipSuccess) return e;
-            if ((e = gram(Q, MX, H)) != hipSuccess) return e;
+            if ((e = gram(Q, MX, H, Yp)) != hipSuccess) return e;
             ksum_begin(st);
             if (p <= LDS_P)
                 k_jacobi_rr_lds<<<1, 1024, 0, st>>>(H, p, rot_cs, rot_ij, rr_misc, rr_misc + 1, sigma);
@@ -1451,10 +1469,11 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
             if ((e = hipMemcpyAsync(theta, sigma, sizeof(double) * p, hipMemcpyDeviceToDevice,
                                     st)) != hipSuccess)
                 return e;
-            k_emb_residual_part<<<(unsigned)chunks, 256, 0, st>>>(xo, mo, theta, ns, p, grows,
-                                                                   part);
+            const int64_t chunks = part_chunks();
+            k_emb_residual_part<<<(unsigned)chunks, 256, 0, st>>>(xo, mo, theta, ns, p,
+                                                                   part_rows(), part_at(Yp));
             k_emb_residual_sum<<<(unsigned)((p + SUM_COLS - 1) / SUM_COLS), 256, 0, st>>>(
-                part, chunks, p, res);
+                part_at(Yp), chunks, p, res);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if ((e = hipMemcpyAsync(h_theta.data(), theta, sizeof(double) * p,
                                     hipMemcpyDeviceToHost, st)) != hipSuccess)
@@ -1502,7 +1521,7 @@ tg_status tg_graphlet_embedding(const int64_t *row_ptr, const int32_t *col, int6
                     R[0], ns, p, q, seed ^ mix64_host(root + (uint64_t)it), R[1]);
                 EMB_CHK(hipGetLastError());
                 p = q;
-                        EMB_CHK(orth(R[1], Yp));
+                EMB_CHK(orth(R[1], Yp));
                 EMB_CHK(orth(Yp, R[2]));
                 EMB_CHK(rayleigh_ritz(R[2], R[0], R[1]));
                 chk = worst();
