@@ -131,7 +131,6 @@ static __device__ __forceinline__ int rank4(int a, int b, int c, int d) {
 
 // Row offsets of the slots [s0, s1) one workgroup takes (flat over the CSR, so
 // that a hub's row is spread over workgroups and short rows fill whole waves).
-constexpr int SLOT_TILE = 2048;
 constexpr int SLOT_ROWS = 1024;
 
 struct SlotTile {

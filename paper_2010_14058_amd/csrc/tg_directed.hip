@@ -35,12 +35,15 @@ namespace {
 __device__ __forceinline__ int dir_code(uint8_t d) { return d == 1 ? 0 : d == 2 ? 1 : 2; }
 
 // One thread per row: bounds, type, entries above the diagonal (the row is
-// searched; k_dir_slots checks that it is sorted).
+// searched; k_dir_slots checks that it is sorted).  Also clears the typed
+// degrees.
 __global__ void __launch_bounds__(256)
 k_dir_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             const uint8_t *__restrict__ types, int64_t n, int64_t nnz, int L,
-            int64_t *__restrict__ ucount, uint32_t *__restrict__ status) {
+            int64_t *__restrict__ ucount, uint32_t *__restrict__ deg3,
+            uint32_t *__restrict__ status) {
     const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t q = u; q < n * 3 * L; q += (int64_t)gridDim.x * 256) deg3[q] = 0u;
     uint32_t bad = 0;
     if (u < n) {
         if (u == 0) ucount[n] = 0;
@@ -72,7 +75,8 @@ constexpr int DIR_TILE_WORDS = 4096;
 __global__ void __launch_bounds__(256)
 k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             const uint8_t *__restrict__ dir, const uint8_t *__restrict__ types, int64_t n,
-            int64_t nnz, int L, uint32_t *__restrict__ deg3, unsigned long long *__restrict__ owners,
+            int64_t nnz, int tile, int L, uint32_t *__restrict__ deg3,
+            unsigned long long *__restrict__ owners,
             uint32_t *__restrict__ status) {
     __shared__ SlotTile T;
     __shared__ uint32_t cnt[DIR_TILE_WORDS];
@@ -80,9 +84,8 @@ k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
     uint64_t own = 0;
     const int tid = threadIdx.x, C = 3 * L;
     uint32_t bad = 0;
-    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
-         s0 += (int64_t)gridDim.x * SLOT_TILE) {
-        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+    for (int64_t s0 = (int64_t)blockIdx.x * tile; s0 < nnz; s0 += (int64_t)gridDim.x * tile) {
+        const int64_t s1 = s0 + tile < nnz ? s0 + tile : nnz;
         slot_tile(rp, n, s0, s1, T);
         const int64_t words = (T.r1 - T.r0 + 1) * C;
         const bool in_lds = words <= DIR_TILE_WORDS;
@@ -138,12 +141,11 @@ __global__ void k_dir_edge_check(const int64_t *__restrict__ eoff, int64_t n, in
 // The canonical edge of each upper slot: esrc[e] = u, eslot[e] = s.
 __global__ void __launch_bounds__(256)
 k_dir_edges_of(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-               const int64_t *__restrict__ eoff, int64_t n, int64_t nnz,
+               const int64_t *__restrict__ eoff, int64_t n, int64_t nnz, int tile,
                int32_t *__restrict__ esrc, int64_t *__restrict__ eslot) {
     __shared__ SlotTile T;
-    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
-         s0 += (int64_t)gridDim.x * SLOT_TILE) {
-        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+    for (int64_t s0 = (int64_t)blockIdx.x * tile; s0 < nnz; s0 += (int64_t)gridDim.x * tile) {
+        const int64_t s1 = s0 + tile < nnz ? s0 + tile : nnz;
         slot_tile(rp, n, s0, s1, T);
         int64_t u = T.r0;
         for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
@@ -523,7 +525,8 @@ DirLayout dir_layout(int64_t n, int64_t nnz, int L, bool own_rows) {
         return at;
     };
     const int64_t m = nnz / 2;
-    y.status = take(256);
+    y.status = take(256);   // followed by acc: cleared together
+    y.acc = take(sizeof(uint64_t) * (size_t)(4 * L * L + 64 * L * L * L));
     y.ucount = take(sizeof(int64_t) * (size_t)(n + 1));
     y.eoff = take(sizeof(int64_t) * (size_t)(n + 1));
     y.stmp = take(sizeof(int64_t) * (size_t)(scan_tiles(n + 1) + 1));
@@ -531,7 +534,6 @@ DirLayout dir_layout(int64_t n, int64_t nnz, int L, bool own_rows) {
     y.esrc = take(sizeof(int32_t) * (size_t)(m > 0 ? m : 1));
     y.eslot = take(sizeof(int64_t) * (size_t)(m > 0 ? m : 1));
     y.rows = take(own_rows ? sizeof(uint64_t) * (size_t)(m > 0 ? m : 1) * 15 * L : 0);
-    y.acc = take(sizeof(uint64_t) * (size_t)(4 * L * L + 64 * L * L * L));
     const size_t m1 = (size_t)(m > 0 ? m : 1);
     y.ckey = take(sizeof(uint64_t) * m1);
     y.ckey_tmp = take(sizeof(uint64_t) * m1);
@@ -559,17 +561,6 @@ unsigned waves_grid(int64_t items) {
         cus > 0 && b > (int64_t)cus * 32)
         b = (int64_t)cus * 32;
     return b > 0 ? (unsigned)b : 1u;
-}
-
-// Workgroups of the flat slot kernels.
-unsigned slots_grid(int64_t nnz) {
-    const int64_t tiles = (nnz + SLOT_TILE - 1) / SLOT_TILE;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        cus > 0 && tiles > (int64_t)cus * 16)
-        return (unsigned)cus * 16;
-    return tiles > 0 ? (unsigned)tiles : 1u;
 }
 
 }  // namespace
@@ -615,18 +606,16 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
 #define DIR_CHK(x) do { if ((x) != hipSuccess) return TG_E_DEVICE; } while (0)
     ksum_reset();
     unsigned long long *owners = reinterpret_cast<unsigned long long *>(status) + 1;
-    DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0, 2, st));
-    DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(acc), 0, width, st));
+    DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0,
+                            (int64_t)((y.acc - y.status) / sizeof(uint64_t)) + width, st));
+    const int cus = device_cus(), tile = slot_tile_size(nnz, cus);
     if (n > 0) {
         ksum_begin(st);
-        // typed degrees start at zero (rounded up to whole 8-byte words of
-        // their 256-byte aligned region)
-        DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(deg3), 0, (n * 3 * L + 1) / 2, st));
         k_dir_nodes<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(row_ptr, col, types, n, nnz, L,
-                                                                 ucount, status);
+                                                                 ucount, deg3, status);
         if (nnz > 0)
-            k_dir_slots<<<slots_grid(nnz), 256, 0, st>>>(row_ptr, col, dir, types, n, nnz, L, deg3,
-                                                         owners, status);
+            k_dir_slots<<<slot_tile_grid(nnz, tile, cus), 256, 0, st>>>(
+                row_ptr, col, dir, types, n, nnz, tile, L, deg3, owners, status);
         ksum_end("dir_check", 0.0, st);
         DIR_CHK(hipGetLastError());
         DIR_CHK(launch_excl_scan(ucount, eoff, n + 1, reinterpret_cast<int64_t *>(w + y.stmp),
@@ -643,7 +632,8 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
     if (bits & ST_TYPE_RANGE) return TG_E_TYPE_RANGE;
     if (bits) return TG_E_NOT_SIMPLE;
     if (m > 0) {
-        k_dir_edges_of<<<slots_grid(nnz), 256, 0, st>>>(row_ptr, col, eoff, n, nnz, esrc, eslot);
+        k_dir_edges_of<<<slot_tile_grid(nnz, tile, cus), 256, 0, st>>>(row_ptr, col, eoff, n, nnz, tile,
+                                                                       esrc, eslot);
         int32_t *hub_id = reinterpret_cast<int32_t *>(w + y.hub_id);
         int32_t *hub_node = reinterpret_cast<int32_t *>(w + y.hub_node);
         unsigned long long *hbits = reinterpret_cast<unsigned long long *>(w + y.hbits);

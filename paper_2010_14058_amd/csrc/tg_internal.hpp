@@ -365,6 +365,22 @@ hipError_t radix_sort(uint64_t *keys, uint64_t *keys_tmp, uint32_t *vals, uint32
                       int64_t count, int end_bit, void *tmp, const uint32_t *gate,
                       hipStream_t st, uint64_t **out_keys, uint32_t **out_vals);
 
+// Slots per tile and workgroups of the kernels that walk the adjacency flat (one
+// thread of 256 per slot and step): 2,048 slots, fewer where that would leave
+// fewer than four workgroups per CU, since a thread's slots are a chain of
+// dependent searches (the directed checks of 16,000 slots in eight workgroups
+// made a call of 8,000 edges 204 us, 169 to 196 us with 63).
+inline int slot_tile_size(int64_t nnz, int64_t cus) {
+    const int64_t t = (nnz + 4 * cus - 1) / (4 * cus);
+    return t >= 2048 ? 2048 : t <= 256 ? 256 : (int)((t + 255) / 256 * 256);
+}
+inline unsigned slot_tile_grid(int64_t nnz, int tile, int64_t cus) {
+    const int64_t tiles = (nnz + tile - 1) / tile;
+    return tiles > cus * 16 ? (unsigned)(cus * 16) : tiles > 0 ? (unsigned)tiles : 1u;
+}
+// Compute units of the current device (256 where the query fails).
+int device_cus();
+
 // Launch wrappers (tg_kernels.hip).
 hipError_t launch_fill_u64(uint64_t *p, uint64_t v, int64_t count, hipStream_t st);
 hipError_t launch_clear_outputs(uint64_t *p, int64_t count, const uint32_t *status,

@@ -75,16 +75,15 @@ k_check_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
 // the wave of its 53,000-neighbour hub.
 __global__ void __launch_bounds__(256)
 k_check_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t n,
-              int64_t nnz, uint32_t *__restrict__ status,
+              int64_t nnz, int tile, uint32_t *__restrict__ status,
               const int32_t *__restrict__ node_graph) {
     __shared__ SlotTile T;
     if (failed_before(status, ST_COL_RANGE | ST_CROSS_GRAPH | ST_SELF_LOOP | ST_UNSORTED |
                                   ST_TYPE_RANGE))
         return;
     uint32_t bad = 0;
-    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
-         s0 += (int64_t)gridDim.x * SLOT_TILE) {
-        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+    for (int64_t s0 = (int64_t)blockIdx.x * tile; s0 < nnz; s0 += (int64_t)gridDim.x * tile) {
+        const int64_t s1 = s0 + tile < nnz ? s0 + tile : nnz;
         slot_tile(rp, n, s0, s1, T);
         int64_t u = T.r0;
         for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
@@ -247,15 +246,14 @@ __global__ void k_relabel(const uint32_t *__restrict__ sorted_ids, const uint8_t
 __global__ void __launch_bounds__(256)
 k_slot_keys(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             const int64_t *__restrict__ ucount, const int64_t *__restrict__ eoff,
-            const int32_t *__restrict__ newid, int64_t n, int64_t nnz, int bits,
+            const int32_t *__restrict__ newid, int64_t n, int64_t nnz, int tile, int bits,
             uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int32_t *__restrict__ ei,
             int32_t *__restrict__ ej, uint32_t *__restrict__ status) {
     __shared__ SlotTile T;
     if (failed_before(status, ST_ASYMMETRIC)) return;  // includes an edge count that is not nnz / 2
     uint32_t bad = 0;
-    for (int64_t s0 = (int64_t)blockIdx.x * SLOT_TILE; s0 < nnz;
-         s0 += (int64_t)gridDim.x * SLOT_TILE) {
-        const int64_t s1 = s0 + SLOT_TILE < nnz ? s0 + SLOT_TILE : nnz;
+    for (int64_t s0 = (int64_t)blockIdx.x * tile; s0 < nnz; s0 += (int64_t)gridDim.x * tile) {
+        const int64_t s1 = s0 + tile < nnz ? s0 + tile : nnz;
         slot_tile(rp, n, s0, s1, T);
         int64_t u = T.r0;
         for (int64_t s = s0 + threadIdx.x; s < s1; s += 256) {
@@ -2309,6 +2307,15 @@ static inline unsigned blocks_bounded(int64_t items, int per_block, int per_cu) 
     return b > 0 ? b : 1;
 }
 
+int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        cus > 0)
+        return cus;
+    return 256;
+}
+
 hipError_t launch_fill_u64(uint64_t *p, uint64_t v, int64_t count, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     int64_t b = (count + 255) / 256;
@@ -2335,8 +2342,9 @@ hipError_t launch_check_rows(const int64_t *rp, const int32_t *col, const uint8_
                                                                   ucount, status, node_graph, gL);
     LAUNCH_CHECK();
     if (nnz == 0) return hipSuccess;
-    k_check_slots<<<blocks_bounded(nnz, SLOT_TILE, 16), 256, 0, st>>>(rp, col, n, nnz, status,
-                                                                     node_graph);
+    const int cus = device_cus(), tile = slot_tile_size(nnz, cus);
+    k_check_slots<<<slot_tile_grid(nnz, tile, cus), 256, 0, st>>>(rp, col, n, nnz, tile, status,
+                                                                  node_graph);
     LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -2378,8 +2386,9 @@ hipError_t launch_slot_keys(const int64_t *rp, const int32_t *col, const int64_t
                             int bits, uint64_t *keys, uint32_t *vals, int32_t *ei, int32_t *ej,
                             uint32_t *status, hipStream_t st) {
     if (nnz == 0) return hipSuccess;
-    k_slot_keys<<<blocks_bounded(nnz, SLOT_TILE, 16), 256, 0, st>>>(
-        rp, col, ucount, eoff, newid, n, nnz, bits, keys, vals, ei, ej, status);
+    const int cus = device_cus(), tile = slot_tile_size(nnz, cus);
+    k_slot_keys<<<slot_tile_grid(nnz, tile, cus), 256, 0, st>>>(
+        rp, col, ucount, eoff, newid, n, nnz, tile, bits, keys, vals, ei, ej, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
