@@ -715,7 +715,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     ea.ctype = ctype;
     ea.tri = tri; ea.ttot = ttot; ea.tdeg = tdeg; ea.tri_slot = tri_slot; ea.A = A; ea.D = D; ea.NC = NC; ea.m = m; ea.L = L;
     ea.agg_u32 = words32 ? 1 : 0;  // A, D and NC entries below 2^32
-    ea.rows = per_edge; ea.gacc = gacc; ea.gw = gw;
+    ea.rows = per_edge; ea.gacc = gacc; ea.gw = gw; ea.gcopy_mask = 0;
     ea.hist_in_lds = (size_t)gw * sizeof(uint64_t) <= 32768 ? 1 : 0;
     // a batch chunk flushes after at most BATCH_EDGE_CHUNK (256) edges, each
     // adding at most 6 * max_deg^2 to one entry (three orbits of a graphlet,
@@ -747,6 +747,16 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
     ea.goff = batch ? batch->goff : nullptr;
     ea.G = batch ? batch->G : 1;
     if (batch) ea.gacc = global_counts;
+    // no room for the histogram in LDS: copies of the accumulators in the
+    // 4-cycle maps' space (free by now)
+    int gcopies = 1;
+    const int64_t map_words = (int64_t)y.heavy_slots * n * L / 2;
+    if (!batch && !pa && !ea.hist_in_lds && map_words >= gw) {
+        while (gcopies < GACC_COPIES && 2 * (int64_t)gcopies * gw <= map_words) gcopies *= 2;
+        ea.gacc = reinterpret_cast<uint64_t *>(maps);
+        ea.gcopy_mask = (unsigned)gcopies - 1;
+        HIPCHK(launch_fill_u64(ea.gacc, 0, (int64_t)gcopies * gw, st));
+    }
     ea.few_list = val_b;
     ea.light_list = le + (m > 0 ? m - 1 : 0);
     uint64_t *xyk = y.defer ? at<uint64_t>(ws, y.off_xyk) : nullptr;
@@ -805,7 +815,7 @@ static tg_status run(const int64_t *row_ptr, const int32_t *col, const uint8_t *
         } else if (batch)
             HIPCHK(launch_batch_finalize(global_counts, batch->gL, batch->goff, batch->G, status, st));
         else if (global_counts)
-            HIPCHK(launch_global_finalize(gacc, L, gw, global_counts, status, st));
+            HIPCHK(launch_global_finalize(ea.gacc, gcopies, L, gw, global_counts, status, st));
         if (!pa) timing_mark("global");
     }
 

@@ -119,7 +119,8 @@ __device__ __forceinline__ void hist_add(const EdgeArgs &a, uint64_t *hist, int 
         if (j < 0) atomicOr(a.status, ST_INTERNAL);
         else atomicAdd((unsigned long long *)&a.gacc[a.goff[g] + j], (unsigned long long)v);
     } else {
-        atomicAdd((unsigned long long *)&a.gacc[idx], (unsigned long long)v);
+        atomicAdd((unsigned long long *)&a.gacc[(size_t)(blockIdx.x & a.gcopy_mask) * a.gw + idx],
+                  (unsigned long long)v);
     }
 }
 

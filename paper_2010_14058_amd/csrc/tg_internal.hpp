@@ -86,6 +86,12 @@ constexpr uint64_t DIRECT_STEPS = uint64_t(1) << 27;
 // up to this many types (type masks in registers), copies of the sums.
 constexpr int GLOBALS_MAX_L = 8;
 constexpr int GLOBALS_COPIES = 64;
+// Most copies of the global accumulators of a single graph whose histogram
+// exceeds LDS (ten types and more): each copy's words are added to from one XCD.
+// With one copy a derivation's time hangs on which L2 channels its few hottest
+// words share, so on where the accumulators lie (1M edges, 12 types: 24.6 or
+// 37.1 ms; 16 types: 38.9 or 34.4 ms); with 16 copies 12.7 and 20.0 ms.
+constexpr int GACC_COPIES = 16;
 
 // Batches of graphs of at most this many nodes are counted graph by graph in
 // LDS when only global counts are asked for (tg_small.hip): 512 rows of 512
@@ -272,6 +278,7 @@ struct EdgeArgs {
     uint64_t *rows;      // may be null
     uint64_t *gacc;      // global accumulators
     int gw;
+    unsigned gcopy_mask; // copies of them (a power of two) less one, by workgroup
     int hist_in_lds;             // 0: global atomics, 1: uint64 LDS histogram, 2: uint32 LDS histogram
     int tcap;                    // light/heavy edge cut on the smaller degree = LDS list size
     int derive_batch;            // edges whose derivation runs together (LDS slots of 4 L^2 words)
@@ -468,7 +475,7 @@ hipError_t launch_edges(bool heavy, const EdgeArgs &args, unsigned grid, hipStre
 hipError_t launch_edge_classes(const EdgeArgs &args, int cus, hipStream_t st, bool cliques = false);
 hipError_t launch_edges_few(const EdgeArgs &args, unsigned grid, hipStream_t st);
 hipError_t launch_derive(const EdgeArgs &args, unsigned grid, hipStream_t st);
-hipError_t launch_global_finalize(const uint64_t *gacc, int L, int gw, uint64_t *out,
+hipError_t launch_global_finalize(const uint64_t *gacc, int copies, int L, int gw, uint64_t *out,
                                   uint32_t *status, hipStream_t st);
 
 

@@ -2245,7 +2245,7 @@ __global__ void __launch_bounds__(LONG_THREADS) k_cyc_work_long(WorkArgs a, int6
 }
 
 // Global counts: divide each graphlet block by its edge count.
-__global__ void k_global_finalize(const uint64_t *__restrict__ gacc, int L,
+__global__ void k_global_finalize(const uint64_t *__restrict__ gacc, int copies, int L,
                                   uint64_t *__restrict__ out, uint32_t *__restrict__ status) {
     if (input_failed(status)) return;
     int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2259,7 +2259,8 @@ __global__ void k_global_finalize(const uint64_t *__restrict__ gacc, int L,
     else if (q < n2 + 2 * n3) h = 2;
     else h = 3 + (q - n2 - 2 * n3) / n4;
     const uint64_t E[9] = {1, 2, 3, 3, 3, 4, 4, 5, 6};
-    uint64_t v = gacc[q];
+    uint64_t v = 0;
+    for (int c = 0; c < copies; ++c) v += gacc[(size_t)c * gw + q];
     if (v % E[h]) atomicOr(status, ST_NOT_DIVISIBLE);
     out[q] = v / E[h];
 }
@@ -2600,9 +2601,9 @@ hipError_t launch_blk(int pass, const CycleArgs &a, const BlkArgs &b, int64_t *s
                      : launch_blk_pass<1>(a, b, scan_tmp, wide, st);
 }
 
-hipError_t launch_global_finalize(const uint64_t *gacc, int L, int gw, uint64_t *out, uint32_t *status,
-                                  hipStream_t st) {
-    k_global_finalize<<<blocks_for(gw, 256), 256, 0, st>>>(gacc, L, out, status);
+hipError_t launch_global_finalize(const uint64_t *gacc, int copies, int L, int gw, uint64_t *out,
+                                  uint32_t *status, hipStream_t st) {
+    k_global_finalize<<<blocks_for(gw, 256), 256, 0, st>>>(gacc, copies, L, out, status);
     LAUNCH_CHECK();
     return hipSuccess;
 }
