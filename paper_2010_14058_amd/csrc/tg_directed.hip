@@ -68,9 +68,10 @@ k_dir_nodes(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
 // half of it for the 53,000-neighbour hub's wave; 2.0 ms with a search per
 // slot.  Only the slots whose neighbour's row is the shorter (ties: the smaller
 // id's) search it: of each pair of opposite slots just one, so when all of them
-// find theirs and they are half of the slots (counted in owners), every other
-// slot has been found as well: 1.16 ms.
+// find theirs and they are half of the slots (counted in DIR_OWNERS words, one
+// atomic per workgroup), every other slot has been found as well: 1.16 ms.
 constexpr int DIR_TILE_WORDS = 4096;
+constexpr int DIR_OWNERS = 16;
 
 __global__ void __launch_bounds__(256)
 k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
@@ -80,10 +81,12 @@ k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
             uint32_t *__restrict__ status) {
     __shared__ SlotTile T;
     __shared__ uint32_t cnt[DIR_TILE_WORDS];
+    __shared__ unsigned long long s_own;
     if (failed_before(status, ST_COL_RANGE | ST_SELF_LOOP | ST_UNSORTED | ST_ASYMMETRIC)) return;
     uint64_t own = 0;
     const int tid = threadIdx.x, C = 3 * L;
     uint32_t bad = 0;
+    if (tid == 0) s_own = 0;   // the tiles' barriers follow
     for (int64_t s0 = (int64_t)blockIdx.x * tile; s0 < nnz; s0 += (int64_t)gridDim.x * tile) {
         const int64_t s1 = s0 + tile < nnz ? s0 + tile : nnz;
         slot_tile(rp, n, s0, s1, T);
@@ -126,16 +129,13 @@ k_dir_slots(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
         __syncthreads();
     }
     own = wave_sum_u64(own);
-    if (lane_id() == 0 && own) atomicAdd(owners, (unsigned long long)own);
     bad = wave_or(bad);
-    if (lane_id() == 0 && bad) atomicOr(status, bad);
-}
-
-__global__ void k_dir_edge_check(const int64_t *__restrict__ eoff, int64_t n, int64_t nnz,
-                                 const unsigned long long *__restrict__ owners,
-                                 uint32_t *__restrict__ status) {
-    if (2 * eoff[n] != nnz || 2 * *owners != (unsigned long long)nnz)
-        atomicOr(status, ST_EDGE_COUNT);
+    if (lane_id() == 0) {
+        if (own) atomicAdd(&s_own, (unsigned long long)own);
+        if (bad) atomicOr(status, bad);
+    }
+    __syncthreads();
+    if (tid == 0 && s_own) atomicAdd(&owners[blockIdx.x % DIR_OWNERS], s_own);
 }
 
 // The canonical edge of each upper slot: esrc[e] = u, eslot[e] = s.
@@ -605,7 +605,8 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
     const int64_t m = nnz / 2, width = tg_directed_global_width(L);
 #define DIR_CHK(x) do { if ((x) != hipSuccess) return TG_E_DEVICE; } while (0)
     ksum_reset();
-    unsigned long long *owners = reinterpret_cast<unsigned long long *>(status) + 1;
+    // the second half of the status words
+    unsigned long long *owners = reinterpret_cast<unsigned long long *>(status) + 16;
     DIR_CHK(launch_fill_u64(reinterpret_cast<uint64_t *>(status), 0,
                             (int64_t)((y.acc - y.status) / sizeof(uint64_t)) + width, st));
     const int cus = device_cus(), tile = slot_tile_size(nnz, cus);
@@ -620,17 +621,19 @@ tg_status tg_count_directed(const int64_t *row_ptr, const int32_t *col, const ui
         DIR_CHK(hipGetLastError());
         DIR_CHK(launch_excl_scan(ucount, eoff, n + 1, reinterpret_cast<int64_t *>(w + y.stmp),
                                  nullptr, st));
-        k_dir_edge_check<<<1, 1, 0, st>>>(eoff, n, nnz, owners, status);
-        DIR_CHK(hipGetLastError());
     } else if (nnz > 0) {
         return TG_E_INVALID_ARG;
     }
-    uint32_t bits = 0;
-    DIR_CHK(hipMemcpyAsync(&bits, status, sizeof(bits), hipMemcpyDeviceToHost, st));
+    uint64_t head[16 + DIR_OWNERS];
+    DIR_CHK(hipMemcpyAsync(head, status, sizeof(head), hipMemcpyDeviceToHost, st));
     DIR_CHK(hipStreamSynchronize(st));
     ksum_collect();
+    uint32_t bits = (uint32_t)head[0];
     if (bits & ST_TYPE_RANGE) return TG_E_TYPE_RANGE;
-    if (bits) return TG_E_NOT_SIMPLE;
+    // every slot has its opposite (so half of them lie above the diagonal)
+    uint64_t pairs = 0;
+    for (int q = 0; q < DIR_OWNERS; ++q) pairs += head[16 + q];
+    if (bits || 2 * pairs != (uint64_t)nnz) return TG_E_NOT_SIMPLE;
     if (m > 0) {
         k_dir_edges_of<<<slot_tile_grid(nnz, tile, cus), 256, 0, st>>>(row_ptr, col, eoff, n, nnz, tile,
                                                                        esrc, eslot);
