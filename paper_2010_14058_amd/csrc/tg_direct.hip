@@ -23,6 +23,8 @@ constexpr int DIRECT_COPIES = 16;
 // Copies of an edge's orbit counters: lanes of one step mostly count the same
 // few type pairs.
 constexpr int ORBIT_COPIES = 4;
+// 32-bit orbit counters (at most one per walk step), 16-bit ids of near nodes.
+static_assert(DIRECT_STEPS <= 0xffffffffu && DIRECT_NODES <= 65536, "counter and id widths");
 
 // Checks of one input row per wave: order, range, self-loops, types, and each
 // neighbour's row holding the mirrored entry; entries above the diagonal;

@@ -1107,6 +1107,8 @@ __device__ __forceinline__ void edges_light_body(const EdgeArgs &a) {
 // edges) the two from 6.4 to 1.1 ms, on a 1M-edge request from 1.5 to 0.55 ms.
 constexpr int FEW_LANES = 8;
 constexpr int FEW_GROUPS = WAVE / FEW_LANES;
+// Its 32-bit sums: at most FEW_MAX counts or degrees below 2^16.
+static_assert((uint64_t)FEW_MAX * 65536 <= 0xffffffffu, "sums of few members in 32 bits");
 
 __global__ void __launch_bounds__(WAVE) k_edges_few(EdgeArgs a) {
     extern __shared__ uint32_t sm_few[];

@@ -37,6 +37,8 @@ constexpr int SMALL_FEW = 4;
 // `nodes` nodes and L types.  Sums of copies stay below 24 C(nodes, 4) (at most
 // 12 paths on four nodes; tailed triangles are met twice), so graphs of at
 // most 256 nodes need only 32-bit sums.
+static_assert((uint64_t)SMALL_MID * (SMALL_MID - 1) * (SMALL_MID - 2) * (SMALL_MID - 3) <= 0xffffffffu,
+              "sums of copies of graphs of SMALL_MID nodes in 32 bits");
 struct SmallLds {
     size_t hist, bits, masks, rank4, rank3, pairs, triples, cnt, pair, scan, deg, row, rank, types, total;
 };
