@@ -341,7 +341,9 @@ def run_batch_workload(args, graphs: int, single_sample: int, oracle_graphs: int
     del graph
     log(f"[bench] batch: eager {eager_s * 1e3 / steps:.1f} ms per call, replay "
         f"{replay_s * 1e3 / steps:.1f} ms per launch, identical={replay_ok}")
-    # the same graphs, one library call each (a prefix of the batch)
+    # the same graphs, one library call each (a prefix of the batch), at the
+    # knobs a program has by default
+    P.set_tuning(**defaults)
     S = min(single_sample, b.G)
     singles = []
     for g in range(S):
