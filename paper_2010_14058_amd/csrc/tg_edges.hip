@@ -1248,7 +1248,7 @@ template <int MODE>
 __global__ void __launch_bounds__(EDGE_THREADS_HEAVY)
 __attribute__((amdgpu_waves_per_eu(MODE == 0 || MODE == 3 ? 5 : 1))) k_edges_heavy(EdgeArgs a) {
     extern __shared__ uint64_t sm_edgeh[];
-    pick_gacc(a);
+    if constexpr (MODE == 1 || MODE == 2) pick_gacc(a);
     __shared__ uint32_t meta[4];
     __shared__ uint32_t wave_cnt[EDGE_THREADS_HEAVY / WAVE];
     __shared__ uint64_t s_idx;
