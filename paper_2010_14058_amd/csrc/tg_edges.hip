@@ -1043,6 +1043,8 @@ __device__ __forceinline__ void edges_light_body(const EdgeArgs &a) {
         const uint64_t count = a.counters[C_EDGE_LIGHT];
         for (uint64_t q = blockIdx.x; q < count; q += gridDim.x) one_edge(a.light_list[-(int64_t)q]);
     } else if (!a.batch) {
+        // eight consecutive edges at a time: one by one measures the same (2.5M
+        // edges with 16 types and hubs: 107.8 and 107.4 ms)
         for (int64_t e0 = (int64_t)blockIdx.x * 8; e0 < a.m; e0 += (int64_t)gridDim.x * 8) {
             uint64_t mask = classify(e0, e0 + 8 < a.m ? e0 + 8 : a.m);
             while (mask) {
