@@ -215,14 +215,15 @@ MULTI_KERNEL_PHASES = {
     for ph in ("cycA_blk", "cycB_blk")}
 
 
-def load_traffic(kernel: str):
-    """Measured HBM bytes per launch of `kernel`, if recorded for this source."""
+def load_traffic(kernel: str, g):
+    """Measured HBM bytes per launch of `kernel`, if recorded for this source
+    and a graph of these sizes."""
     path = os.path.join(ROOT, "profiles", f"traffic_{kernel}.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         rec = json.load(f)
-    if rec.get("source_sha") != kernel_source_sha():
+    if rec.get("source_sha") != kernel_source_sha() or rec.get("graph") != [g.n, g.m, g.L]:
         return None
     return rec.get("bytes_per_launch")
 
@@ -667,7 +668,7 @@ def roofline_of(P, torch, g, rows, stats, phase_avg, peak_stream):
              "cycB_heavy": ("wedge", stats["heavy_wedges_pass_b"] - wbk),
              "cycA_blk": ("wedge", wak), "cycB_blk": ("wedge", wbk)}.get(dom, ("edge", g.m))
     roof = {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS,
-            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": load_traffic(dom),
+            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": load_traffic(dom, g),
             "avg_ms": dom_ms, "algorithmic_bytes_per_launch": abytes[dom],
             "work_unit": units[0], "units_per_launch": int(units[1]),
             "streaming_peak_GBps": peak_stream, "frac_of_streaming_peak":
@@ -679,7 +680,7 @@ def roofline_of(P, torch, g, rows, stats, phase_avg, peak_stream):
     for k in MULTI_KERNEL_PHASES:
         if k in per_kernel:
             per_kernel[k]["kernels"] = MULTI_KERNEL_PHASES[k]
-            per_kernel[k]["traffic"] = load_traffic(k)
+            per_kernel[k]["traffic"] = load_traffic(k, g)
             if k in scratch:
                 per_kernel[k]["scratch_bytes"] = scratch[k]
     return roof, per_kernel, over, abytes
